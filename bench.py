@@ -173,14 +173,18 @@ def kernel_name(B, grouped=False, rows_per_panel=1024, e4m3=False, g128=False):
         return f"grouped_gemv_kernel<{rows_per_panel // 128}, true, true>"
     if g128:
         return "grouped_gemv_kernel<4, true, true, true>"
+    if grouped and 2 <= B <= 4:
+        return f"tern_mfma_kernel<2, 8, 2, {f8}, false>"  # two result blocks of activation digits
     if grouped and B > 1:
         # hi/lo activation halves in one or two MFMAs
         return f"grouped_mma_kernel<{1 if B <= 8 else 2}, {f8}>"
     if grouped:
         return f"grouped_gemv_kernel<{rows_per_panel // 128}, {f8}, false>"  # 8 waves x 16 rows per row block
     # one matrix per launch (qtea_gemm_lowbatch): the same kernels in their single-problem form
+    if 2 <= B <= 8:
+        return f"tern_mfma_kernel<{2 if B <= 4 else 3}, 8, 1, {f8}, true>"
     if B > 1:
-        return f"grouped_mma_kernel<{1 if B <= 8 else 2}, {f8}, true>"
+        return f"grouped_mma_kernel<2, {f8}, true>"
     return f"grouped_gemv_kernel<4, {f8}, {'true' if g128 else 'false'}, true>"
 
 

@@ -872,7 +872,7 @@ static_assert(GLds<kOneRB>::RP == kRowsPerRB * kOneRB && GLds<kMaxRB>::RP == kRo
               "panel heights of the planner");
 bool one_shape(const qtea_desc& d, int batch, OneShape* o) {
   return one_shape_for(d, batch, batch == 1 ? grid_size() : cu_count(),
-                       batch == 1 ? GLds<kOneRB>::RP : one_mma_rows_per_panel(batch), o);
+                       batch == 1 ? GLds<kOneRB>::RP : one_mma_rows_per_panel(), o);
 }
 
 template <bool F8, bool G128>
@@ -896,7 +896,7 @@ int one_launch(const qtea_desc& d, const void* packed, const uint16_t* X, int ba
   one.batch = batch;
   hipError_t e;
   if (batch > 1)
-    e = launch_one_mma(one, o.grid, f8, part, counters, st);
+    e = launch_one_mma(one, o.grid, f8, part, st);
   else if (g128)
     e = launch_one_b1<true, true>(one, o.grid, part, counters, st);
   else

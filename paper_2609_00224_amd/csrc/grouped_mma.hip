@@ -1,5 +1,6 @@
-// Grouped low-batch GEMM on the matrix cores: Y_m = X_m W_m^T for 2 <= B <=
-// 16 activation rows per problem (Eq. 10 with one group and zero bias, plus
+// Grouped low-batch GEMM on the matrix cores: Y_m = X_m W_m^T for 5 <= B <=
+// 16 activation rows per problem (and 9 <= B <= 16 rows of one problem on its
+// own; smaller batches run the kernel of tern_mfma.hip) (Eq. 10 with one group and zero bias, plus
 // the Eq. 11 residual), every problem of a plan in one persistent launch.
 //
 // At batch B the product is a dense contraction of the ternary weights with
@@ -60,11 +61,10 @@ namespace {
 // register budget (168 instead of 128 per lane) takes its spills from about
 // 40 registers to 5 (8B stack, batch 16: 827 -> 720 us per token; at NB = 1
 // the 768-thread shape, with no spills to remove, lost 25 % to the fewer
-// waves).  One matrix on its own: 512 threads at both (256 registers, no
-// spills, and twice the panels of a short launch to spread over the CUs:
-// the 8B stack chained at batch 4 / 8 / 16 takes 2104 / 2178 / 2685 us
-// against 2406 / 2560 / 3314 with the grouped shapes; 256 threads were
-// slower again).
+// waves).  One matrix on its own (NB = 2): 512 threads (256 registers, no
+// spills, and more panels of a short launch to spread over the CUs: the 8B
+// stack chained at batch 16 takes 2685 us against 3314 with the grouped
+// shape; 256 threads were slower again).
 template <int NB, bool ONE>
 struct MShape {
   static constexpr int MT = ONE ? 512 : (NB == 1 ? 1024 : 768);  // threads per workgroup
@@ -191,8 +191,7 @@ __device__ __forceinline__ void split_hl(float a, _Float16& hi, _Float16& lo) {
 // stood between every split panel and its output).
 template <int NB, bool F8, bool ONE = false>
 __global__ __launch_bounds__((MShape<NB, ONE>::MT)) void grouped_mma_kernel(const uint8_t* __restrict__ plan,
-                                                          float* __restrict__ part,
-                                                          uint32_t* __restrict__ counters, const GOne one) {
+                                                          float* __restrict__ part, const GOne one) {
   using L = MLds<NB>;
   constexpr int kMT = MShape<NB, ONE>::MT, kMRP = MShape<NB, ONE>::MRP;
   constexpr int BP = 8 * NB;  // batch rows per hi (or lo) column set
@@ -696,7 +695,7 @@ __global__ __launch_bounds__(RP / 4 * kRedGroups) void one_reduce_kernel(const G
 }
 
 template <int NB, bool F8, bool ONE>
-hipError_t launch(const uint8_t* plan, int grid, float* part, uint32_t* counters, const GOne& one, hipStream_t st) {
+hipError_t launch(const uint8_t* plan, int grid, float* part, const GOne& one, hipStream_t st) {
   static bool done = false;
   if (!done) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_mma_kernel<NB, F8, ONE>),
@@ -705,37 +704,44 @@ hipError_t launch(const uint8_t* plan, int grid, float* part, uint32_t* counters
     done = true;
   }
   hipLaunchKernelGGL((grouped_mma_kernel<NB, F8, ONE>), dim3(grid), dim3(MShape<NB, ONE>::MT), MLds<NB>::BYTES, st, plan, part,
-                     counters, one);
+                     one);
   return hipGetLastError();
 }
 
 }  // namespace
 
 int grouped_mma_rows_per_panel(int batch) { return batch <= 8 ? MShape<1, false>::MRP : MShape<2, false>::MRP; }
-int one_mma_rows_per_panel(int batch) { return batch <= 8 ? MShape<1, true>::MRP : MShape<2, true>::MRP; }
+int one_mma_rows_per_panel() { return MShape<2, true>::MRP; }
 
 hipError_t launch_grouped_mma(const uint8_t* plan, int grid, int batch, bool f8, float* part, hipStream_t st) {
   const GOne none{};
-  if (f8) return batch <= 8 ? launch<1, true, false>(plan, grid, part, nullptr, none, st)
-                            : launch<2, true, false>(plan, grid, part, nullptr, none, st);
-  return batch <= 8 ? launch<1, false, false>(plan, grid, part, nullptr, none, st)
-                    : launch<2, false, false>(plan, grid, part, nullptr, none, st);
+  // Batch 2..4: the FP4 kernel (8B stack, E4M3, batch 4: 385 against 476 us per
+  // call).  At 5..8 its third result block and digit images cost more than
+  // this kernel's, which is the same at 2 and at 8 (16 layers of the 8B stack
+  // at batch 8: 255 against 226 us).
+  if (batch <= kGroupedTernBatch) return launch_grouped_tern(plan, grid, f8, part, st);
+  if (f8) return batch <= 8 ? launch<1, true, false>(plan, grid, part, none, st)
+                            : launch<2, true, false>(plan, grid, part, none, st);
+  return batch <= 8 ? launch<1, false, false>(plan, grid, part, none, st)
+                    : launch<2, false, false>(plan, grid, part, none, st);
 }
 
-hipError_t launch_one_mma(const GOne& one, int grid, bool f8, float* part, uint32_t* counters, hipStream_t st) {
+hipError_t launch_one_mma(const GOne& one, int grid, bool f8, float* part, hipStream_t st) {
+  // Batch 2..8: the FP4 kernel, whose decode table is a third of this one's
+  // and whose decode is one LDS read per byte (4096 x 4096, batch 2 / 4 / 8:
+  // 9.4 / 9.5 / 11.0 us against 11.5 / 11.9 / 12.0; 28672 x 4096: 16.2 / 16.9 /
+  // 21.5 against 19.7 / 19.9 / 21.7, the reduce kernel included).  Above, six
+  // result blocks would not fit its registers.
   hipError_t e;
-  if (f8) e = one.batch <= 8 ? launch<1, true, true>(nullptr, grid, part, counters, one, st)
-                             : launch<2, true, true>(nullptr, grid, part, counters, one, st);
-  else e = one.batch <= 8 ? launch<1, false, true>(nullptr, grid, part, counters, one, st)
-                          : launch<2, false, true>(nullptr, grid, part, counters, one, st);
+  if (one.batch <= kOneTernBatch) e = launch_one_tern(one, grid, f8, part, st);
+  else e = f8 ? launch<2, true, true>(nullptr, grid, part, one, st) : launch<2, false, true>(nullptr, grid, part, one, st);
   if (e != hipSuccess) return e;
   bool split = false;
   const int64_t ns = one.pr.n_slices;
   for (int p = 0; p < one.pr.n_panels && !split; ++p)
     split = one_owner(p * ns, one.n_units, grid) != one_owner(p * ns + ns - 1, one.n_units, grid);
   if (!split) return hipSuccess;
-  constexpr int RP = MShape<1, true>::MRP;
-  static_assert(MShape<2, true>::MRP == RP, "one panel height for one-matrix launches");
+  constexpr int RP = MShape<2, true>::MRP;
   hipLaunchKernelGGL(one_reduce_kernel<RP>, dim3(one.pr.n_panels, one.batch), dim3(RP / 4 * kRedGroups), 0, st, one,
                      part, grid);
   return hipGetLastError();

@@ -119,17 +119,23 @@ __device__ __forceinline__ Cursor advance(Cursor c, const GProblem* P) {
 constexpr int kBufferWord3 = 0x00020000;
 constexpr int kAuxNT = 2;
 
-// Device-side launches of the low-batch kernels (grouped_mma.hip): the
-// persistent matrix-core kernel for 2 <= batch <= 16 over `grid`
-// workgroups, and its static shared-memory size.
+// The FP4 matrix-core kernel (tern_mfma.hip): a plan of batch 2..kGroupedTernBatch
+// (1024-row panels), or one problem of batch 2..kOneTernBatch (512-row panels;
+// the caller sums the parts of split panels).
+constexpr int kGroupedTernBatch = 4;
+constexpr int kOneTernBatch = 8;
+hipError_t launch_grouped_tern(const uint8_t* plan, int grid, bool f8, float* part, hipStream_t st);
+hipError_t launch_one_tern(const GOne& one, int grid, bool f8, float* part, hipStream_t st);
+
+// The low-batch launches (grouped_mma.hip): a plan of batch 2..16 over `grid`
+// workgroups, and one problem (one.batch rows; split panels summed by a
+// second kernel), each by the kernel that is faster at its batch.
 hipError_t launch_grouped_mma(const uint8_t* plan, int grid, int batch, bool f8, float* part, hipStream_t st);
-// The same kernel on one problem (one.batch rows), `grid` workgroups, split
-// panels finished by their last workgroup (counters: one word per panel).
-hipError_t launch_one_mma(const GOne& one, int grid, bool f8, float* part, uint32_t* counters, hipStream_t st);
-// Rows per panel of the matrix-core kernel at `batch` (2..16): grouped
-// launches, and one matrix on its own.
+hipError_t launch_one_mma(const GOne& one, int grid, bool f8, float* part, hipStream_t st);
+// Rows per panel of the low-batch kernels: grouped launches at `batch`
+// (2..16), and one matrix on its own.
 int grouped_mma_rows_per_panel(int batch);
-int one_mma_rows_per_panel(int batch);
+int one_mma_rows_per_panel();
 
 }  // namespace qtea_grouped
 
