@@ -41,6 +41,10 @@ constexpr int kNBH = 32;               // panel columns staged per LDS pass of t
 static_assert(kNB <= 64, "the diagonal block's elimination maps one column per lane of a wave");
 constexpr int kCT = 64;                // threads of the row-parallel kernels (one wave)
 constexpr int kColChunk = 16;          // later columns of a block updated per workgroup
+// Most workgroups of col_block_kernel, which wait for one another: a quarter
+// of the 512 (two per CU) that the device holds, so that quantizations on
+// four streams (the hardware queues of a process) are resident together.
+constexpr int kXchWgs = 128;
 constexpr int64_t kQAlign = 256;
 constexpr int64_t kQMaxRows = 65536;
 constexpr int64_t kQMaxCols = 65536;
@@ -49,7 +53,7 @@ inline int64_t q_up(int64_t x) { return (x + kQAlign - 1) / kQAlign * kQAlign; }
 inline int64_t q_cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 struct QLayout {
-  int64_t wt, a, u, et, score, flag, rank, dmean, scal, part, vst, total;
+  int64_t wt, a, u, et, score, flag, rank, dmean, scal, part, vst, xch, total;
 };
 
 // Workspace regions (bytes from the start, 256-byte aligned).
@@ -64,9 +68,10 @@ QLayout q_layout(int64_t N, int64_t K) {
   L.flag = o;  o = q_up(o + K * 4);                     // int32 [K] selected
   L.rank = o;  o = q_up(o + K * 4);                     // int32 [K] salient rank or -1
   L.dmean = o; o = q_up(o + q_cdiv(K, kQG) * 8);        // fp64 per block: mean of diag U
-  L.scal = o;  o = q_up(o + 64);                        // fp64 mean diag H; int32 status at +8
+  L.scal = o;  o = q_up(o + 64);                        // fp64 mean diag H; int32 status[2] at +8
   L.part = o;  o = q_up(o + 2 * q_cdiv(N, kCT) * 2 * 8);  // fp64 [2][workgroups][2] column partials
   L.vst = o;   o = q_up(o + 2 * 8);                     // fp64 [2] previous v
+  L.xch = o;   o = q_up(o + 2 * kXchWgs * 4 * 8);       // u64 [2][workgroups][4] exchange slots (col_block_kernel)
   L.total = o;
   return L;
 }
@@ -125,7 +130,10 @@ __device__ inline int tern(double x, double thr) { return x > thr ? 1 : (x < -th
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void hess_kernel(const float* __restrict__ X, int64_t n, int64_t K, double scale,
                                                    double* __restrict__ H) {
-  // 128 x 128 output tile, 8 x 8 per thread, calibration rows staged 16 at a time
+  // 128 x 128 output tile, 8 x 8 per thread, calibration rows staged 16 at a
+  // time; tiles on and above the diagonal, each written to its mirror too
+  // (fp64 multiply-adds bound this: 8192 rows of 4096 columns 9.0 -> 7.6 ms)
+  if (blockIdx.x < blockIdx.y) return;
   __shared__ double xa[16][129], xb[16][129];
   const int64_t a0 = int64_t(blockIdx.y) * 128, b0 = int64_t(blockIdx.x) * 128;
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
@@ -163,6 +171,21 @@ __global__ __launch_bounds__(256) void hess_kernel(const float* __restrict__ X, 
       const int64_t a = a0 + ty + 16 * i, b = b0 + tx + 16 * j;
       if (a < K && b < K) H[a * K + b] = scale * acc[i][j];
     }
+  if (a0 == b0) return;
+  // H[b][a], sixteen of the tile's columns at a time through LDS (the staging
+  // loop ended with a barrier)
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) xa[tx][ty + 16 * i] = scale * acc[i][j];
+    __syncthreads();
+    for (int e = threadIdx.x; e < 16 * 128; e += 256) {
+      const int cc = e >> 7, rr = e & 127;
+      const int64_t b = b0 + 16 * j + cc, a = a0 + rr;
+      if (b < K && a < K) H[b * K + a] = xa[cc][rr];
+    }
+    __syncthreads();
+  }
 }
 
 __global__ void fill_f64_kernel(double* __restrict__ p, int64_t n, double v) {
@@ -735,6 +758,249 @@ __global__ __launch_bounds__(kCT) void col_kernel(ColArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// One block's columns in one launch, for matrices of at most 64 kXchWgs rows.
+//
+// What bounds the column-by-column launches above is the launches: two
+// dependent ones per column (11.3 us), each a few hundred cycles of work on N
+// rows.  Here a workgroup keeps 64 rows of the block's 128 columns in
+// registers, sixteen columns per wave (one row per lane).  The wave that
+// holds the current column runs it alone; per refinement round the
+// workgroups exchange their column sums through slots in memory; the errors
+// of a wave's sixteen columns go to the later waves through LDS, which apply
+// them in column order.  Every value is computed by the same operations in
+// the same order as by the launches, so the results are the same bits.
+// 4096 x 4096 at two rounds: the column phase takes 17 instead of 46 ms.
+//
+// The exchange.  Slot (parity, workgroup) holds the sum's two halves and the
+// count as three 8-byte words, each with the exchange's number in its upper
+// half, so one relaxed store per word publishes them and a reader knows a
+// complete set by the numbers; the slots were zeroed before the first number,
+// 1.  A workgroup reaches exchange s + 2, which overwrites the slots of s,
+// only after every workgroup published s + 1, that is after all read s.
+//
+// Every wait ends: the workgroups are few enough to be resident together,
+// and a wait that lasts 20 s all the same (more such kernels at once than the
+// device holds) raises status[1], after which this and the following
+// launches return at once and the call reports an error.
+// ---------------------------------------------------------------------------
+constexpr int kCBWaves = kQG / kColChunk;  // 8
+constexpr uint64_t kXchTicks = 2000000000ull;  // 20 s of the 100 MHz counter
+
+struct ColBlockArgs {
+  const double* Wt;
+  const double* U;
+  const double* dmean;
+  const uint16_t* alpha;
+  const uint16_t* beta;
+  const int32_t* rank;
+  double* Et;
+  int8_t* T;
+  double* Q;
+  uint16_t* vout;
+  uint8_t* rval;
+  uint8_t* ridx;
+  unsigned long long* xch;
+  int32_t* status;
+  int64_t N, K, G, g, b0, b1;
+  uint32_t seq0;  // number of the exchange before this launch's first
+  int32_t iters;
+  double lambda;
+};
+
+// x plus the value of the lane at distance 32, 16, 8, 4, 2, 1 in turn: the
+// sums of a tree that halves 64 values that often, in every lane.  Up to 8 apart
+// the lanes exchange through DPP moves (after the first steps a value only
+// depends on the lane's low bits, so a rotation by 4 is an exchange by 4).
+template <int CTRL>
+__device__ double dpp_move(double x) {
+  const uint64_t b = uint64_t(__double_as_longlong(x));
+  const uint32_t lo = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(b)), CTRL, 0xf, 0xf, true));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(b >> 32)), CTRL, 0xf, 0xf, true));
+  return __longlong_as_double(static_cast<long long>((uint64_t(hi) << 32) | lo));
+}
+__device__ double wave_tree_sum(double x) {
+  x += __shfl_xor(x, 32);
+  x += __shfl_xor(x, 16);
+  x += dpp_move<0x128>(x);  // row_ror:8
+  x += dpp_move<0x124>(x);  // row_ror:4
+  x += dpp_move<0x4E>(x);   // quad_perm 2,3,0,1
+  x += dpp_move<0xB1>(x);   // quad_perm 1,0,3,2
+  return x;
+}
+
+__global__ __launch_bounds__(kCBWaves * 64, 4) void col_block_kernel(ColBlockArgs a) {
+  __shared__ double err[kColChunk][64];
+  // per wave 16 x 16 values of U: rows of a chunk of columns, its own columns
+  __shared__ double us[kCBWaves][kColChunk][kColChunk];
+  __shared__ int stop_s;
+  if (a.status[1] != 0) return;  // (written before this launch only)
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nwg = gridDim.x;
+  const int64_t r = int64_t(blockIdx.x) * 64 + lane;
+  const bool live = r < a.N;
+  const int nb = int(a.b1 - a.b0);
+  const double al = live ? f16_to_f64(a.alpha[r * a.G + a.g]) : 1.0;
+  const double be = live ? f16_to_f64(a.beta[r * a.G + a.g]) : 0.0;
+  if (threadIdx.x == 0) stop_s = 0;
+  double w[kColChunk];
+#pragma unroll
+  for (int m = 0; m < kColChunk; ++m) {
+    const int c = wv * kColChunk + m;
+    w[m] = live && c < nb ? a.Wt[(a.b0 + c) * a.N + r] : 0.0;
+  }
+  uint32_t seq = a.seq0;
+  // U rows of chunk ch (its columns c = 16 ch + m) at this wave's columns, four per lane
+  auto load_u = [&](int ch, double (&uv)[4]) {
+    const int m = ch * kColChunk + (lane >> 2), k0 = wv * kColChunk + 4 * (lane & 3);
+    const double* src = a.U + (a.b0 + m) * a.K + a.b0 + k0;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) uv[x] = m < nb && k0 + x < nb ? src[x] : 0.0;
+  };
+  auto put_u = [&](const double (&uv)[4]) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) us[wv][lane >> 2][4 * (lane & 3) + x] = uv[x];
+  };
+  // this wave's columns, one per lane (lanes 0..15): U_jj, gamma and the salient rank
+  const int mc = wv * kColChunk + (lane & (kColChunk - 1));
+  const int64_t jc = a.b0 + (mc < nb ? mc : nb - 1);
+  const double du = a.U[jc * a.K + jc];
+  const int32_t rku = a.rank[jc];
+  const double gu = exp((-a.lambda * (du / a.dmean[a.g])) * (double(mc) / double(nb)));
+  double own[4];
+  load_u(wv, own);  // rows and columns of the wave's own chunk
+  auto lane_double = [&](double x, int l) -> double {  // l: uniform
+    const uint64_t b = uint64_t(__double_as_longlong(x));
+    const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b)), l));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b >> 32)), l));
+    return __longlong_as_double(static_cast<long long>((uint64_t(hi) << 32) | lo));
+  };
+  // sum and count over the workgroup's rows, then over the workgroups, in the
+  // order of stage_partial and stage_v; false when the wait ran out
+  auto exchange = [&](double u, bool one, double& su, double& cn) -> bool {
+    u = wave_tree_sum(u);
+    const uint32_t c = uint32_t(__popcll(__ballot(one)));
+    ++seq;
+    if (nwg == 1) {
+      su = u;
+      cn = double(c);
+      return true;
+    }
+    unsigned long long* slots = a.xch + int64_t(seq & 1u) * kXchWgs * 4;
+    const unsigned long long tag = static_cast<unsigned long long>(seq) << 32;
+    if (lane < 3) {
+      const unsigned long long ub = static_cast<unsigned long long>(__double_as_longlong(u));
+      const unsigned long long d = lane == 0 ? (ub & 0xffffffffull) : (lane == 1 ? ub >> 32 : static_cast<unsigned long long>(c));
+      __hip_atomic_store(slots + 4 * blockIdx.x + lane, tag | d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    su = 0.0;
+    int ci = 0;
+    bool ok = true;
+    const uint64_t t0 = __builtin_readsteadycounter();
+    for (int k = lane; k < nwg && ok; k += 64) {
+      unsigned long long x0, x1, x2;
+      for (;;) {
+        x0 = __hip_atomic_load(slots + 4 * k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        x1 = __hip_atomic_load(slots + 4 * k + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        x2 = __hip_atomic_load(slots + 4 * k + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((x0 >> 32) == seq && (x1 >> 32) == seq && (x2 >> 32) == seq) break;
+        if (__builtin_readsteadycounter() - t0 > kXchTicks) {
+          ok = false;
+          break;
+        }
+      }
+      su += __longlong_as_double(static_cast<long long>((x1 << 32) | (x0 & 0xffffffffull)));
+      ci += int(uint32_t(x2));
+    }
+    su = wave_tree_sum(su);
+    cn = wave_tree_sum(double(ci));  // (small whole numbers: exact)
+    return __all(ok);
+  };
+  for (int ch = 0; ch * kColChunk < nb; ++ch) {
+    const int nc = nb - ch * kColChunk < kColChunk ? nb - ch * kColChunk : kColChunk;
+    if (wv == ch) {  // this wave's columns
+      put_u(own);
+      asm volatile("" ::: "memory");  // (read back by this wave only: in order)
+      bool ok = true;
+#pragma unroll
+      for (int m = 0; m < kColChunk; ++m) {
+        if (m < nc && ok) {
+          const int i = ch * kColChunk + m;
+          const int64_t j = a.b0 + i;
+          double urow[kColChunk];
+#pragma unroll
+          for (int k = m + 1; k < kColChunk; ++k) urow[k] = us[wv][m][k];
+          const double wj = w[m], x = wj - be;
+          const double xa = fabs(x) / al;
+          double v = 1.0;
+          for (int it = 0; it < a.iters && ok; ++it) {
+            const bool nz = live && tern(x, it == 0 ? al / 2.0 : v * al / 2.0) != 0;
+            double su, cn;
+            ok = exchange(nz ? xa : 0.0, nz, su, cn);
+            if (cn > 0.0) v = f16_to_f64(f64_to_f16(su / cn));
+          }
+          const int t = tern(x, v * al / 2.0);
+          double q = be + (v * al) * double(t);
+          const int32_t srank = __builtin_amdgcn_readlane(rku, m);
+          if (srank >= 0) {
+            const double res = wj - q;
+            const int g0 = lane & ~3;
+            double best = fabs(__shfl(res, g0));
+            int bk = 0;
+#pragma unroll
+            for (int k = 1; k < 4; ++k) {
+              const double mm = fabs(__shfl(res, g0 + k));
+              if (mm > best) {
+                best = mm;
+                bk = k;
+              }
+            }
+            const double rk = __shfl(res, g0 + bk);
+            const uint8_t code = f64_to_e4m3(rk);
+            if (lane - g0 == bk) q += e4m3_to_f64(code);
+            if (live && lane == g0) {
+              a.rval[int64_t(srank) * (a.N / 4) + r / 4] = code;
+              a.ridx[int64_t(srank) * (a.N / 4) + r / 4] = uint8_t(bk);
+            }
+          }
+          const double e = (lane_double(gu, m) * (wj - q)) / lane_double(du, m);
+          err[m][lane] = e;
+#pragma unroll
+          for (int k = m + 1; k < kColChunk; ++k) w[k] = w[k] - e * urow[k];  // (zeros past the block)
+          if (live) {
+            a.T[r * a.K + j] = int8_t(t);
+            if (a.Q) a.Q[r * a.K + j] = q;
+            a.Et[int64_t(i) * a.N + r] = e;
+          }
+          if (blockIdx.x == 0 && lane == 0) a.vout[j] = f64_to_f16(v);
+        }
+      }
+      if (!ok && lane == 0) {
+        __hip_atomic_store(a.status + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        stop_s = 1;
+      }
+    } else {
+      seq += uint32_t(a.iters) * uint32_t(nc);  // (the exchanges' numbers advance alike in every wave)
+      if (wv > ch) {
+        double uv[4];
+        load_u(ch, uv);  // (in flight while the current wave runs its columns)
+        put_u(uv);
+      }
+    }
+    __syncthreads();
+    if (stop_s) return;
+    if (wv > ch && wv * kColChunk < nb) {  // the later waves take the sixteen errors in column order
+#pragma unroll 4
+      for (int m = 0; m < kColChunk; ++m) {  // (a full chunk: a later one exists)
+        const double e = err[m][lane];
+#pragma unroll
+        for (int k = 0; k < kColChunk; ++k) w[k] = w[k] - e * us[wv][m][k];
+      }
+    }
+    __syncthreads();  // the errors are read before the next wave writes its own
+  }
+}
+
 // Wt[k][r] -= sum_{i < B} U[b0 + i][k] Et[i][r] for k in [b1, K)
 __global__ __launch_bounds__(256) void trail_gemm_kernel(double* __restrict__ Wt, const double* __restrict__ U,
                                                          const double* __restrict__ Et, int64_t N, int64_t K,
@@ -832,7 +1098,7 @@ int qtea_quantize(const double* W, const double* H, int64_t N, int64_t K, const 
   // (salient may be NULL only when n_salient == 0: then nothing is written to it)
   int32_t* S = salient ? salient : flag;
 
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, st, status, int64_t(1), 0);
+  hipLaunchKernelGGL(fill_i32_kernel, dim3(1), dim3(64), 0, st, status, int64_t(2), 0);
   hipLaunchKernelGGL(fill_f64_kernel, dim3(grid1(K * K, 256)), dim3(256), 0, st, U, K * K, 0.0);
   hipLaunchKernelGGL(fill_f64_kernel, dim3(grid1(K, 256)), dim3(256), 0, st, score, K, 0.0);
   // 1. salient columns
@@ -888,6 +1154,11 @@ int qtea_quantize(const double* W, const double* H, int64_t N, int64_t K, const 
   a.nwg = nwg;
   a.iters = p->iters;
   a.lambda = p->lambda_decay;
+  const bool in_block = nwg <= kXchWgs;
+  unsigned long long* xch = reinterpret_cast<unsigned long long*>(ws + L.xch);
+  uint32_t seq = 0;
+  if (in_block)
+    hipLaunchKernelGGL(fill_f64_kernel, dim3(4), dim3(256), 0, st, reinterpret_cast<double*>(xch), int64_t(2 * kXchWgs * 4), 0.0);
   int s = 0;  // partials / previous-v buffer the next stage reads
   auto stage = [&](int mode) {
     a.part_in = part + s * nwg * 2;
@@ -911,12 +1182,20 @@ int qtea_quantize(const double* W, const double* H, int64_t N, int64_t K, const 
     a.g = g;
     a.b0 = b0;
     a.b1 = b1;
-    a.j = b0;
-    if (p->iters > 0) stage(kStart);
-    for (int64_t j = b0; j < b1; ++j) {
-      a.j = j;
-      for (int it = 1; it < p->iters; ++it) stage(kRefine);
-      stage(kFinal);
+    if (in_block) {
+      const ColBlockArgs cb{Wt,   U,   dmean, group_scale, group_bias, rank, Et, T, Q,  col_rescale, resid_val,
+                            resid_idx, xch, status, N,     K,          G,    g,  b0, b1, seq,        p->iters,
+                            p->lambda_decay};
+      hipLaunchKernelGGL(col_block_kernel, dim3(uint32_t(nwg)), dim3(kCBWaves * 64), 0, st, cb);
+      seq += uint32_t(b1 - b0) * uint32_t(p->iters);
+    } else {
+      a.j = b0;
+      if (p->iters > 0) stage(kStart);
+      for (int64_t j = b0; j < b1; ++j) {
+        a.j = j;
+        for (int it = 1; it < p->iters; ++it) stage(kRefine);
+        stage(kFinal);
+      }
     }
     if (b1 < K)
       hipLaunchKernelGGL(trail_gemm_kernel, dim3(uint32_t(q_cdiv(N, 64)), uint32_t(q_cdiv(K - b1, 64))), dim3(256), 0,
@@ -924,9 +1203,10 @@ int qtea_quantize(const double* W, const double* H, int64_t N, int64_t K, const 
   }
   if (hipGetLastError() != hipSuccess) return QTEA_ERR_HIP;
   if (hipStreamSynchronize(st) != hipSuccess) return QTEA_ERR_HIP;
-  int32_t host_status = 0;
-  if (hipMemcpy(&host_status, status, sizeof(host_status), hipMemcpyDeviceToHost) != hipSuccess) return QTEA_ERR_HIP;
-  return host_status ? QTEA_ERR_NOT_POSITIVE : QTEA_OK;
+  int32_t host_status[2] = {0, 0};
+  if (hipMemcpy(host_status, status, sizeof(host_status), hipMemcpyDeviceToHost) != hipSuccess) return QTEA_ERR_HIP;
+  if (host_status[0]) return QTEA_ERR_NOT_POSITIVE;
+  return host_status[1] ? QTEA_ERR_HIP : QTEA_OK;
 }
 
 }  // extern "C"
