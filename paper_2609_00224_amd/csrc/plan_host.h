@@ -177,6 +177,10 @@ inline bool offsets_fit(const qtea_desc& d) {
 // same number of units (the least that fits the grid), so no workgroup
 // carries more than the others.  The workspace holds one arrival counter
 // per panel (used at batch 1), then two partial-row slots per workgroup.
+// The counters have the same place for every matrix (up to kOneCounterBytes of
+// them): a workspace serves a sequence of matrices, and one matrix's
+// counters must not lie in another's part of the partial rows.
+constexpr int64_t kOneCounterBytes = 65536;
 struct OneShape {
   int rp, n_panels, n_slices, grid;
   int64_t n_units, off_part, ws_bytes;
@@ -187,7 +191,7 @@ inline bool one_shape_for(const qtea_desc& d, int batch, int max_wg, int rp, One
   o->n_units = units_for(d, o->rp, &o->n_slices, &o->n_panels);
   const int64_t per = cdiv(o->n_units, max_wg);
   o->grid = int(cdiv(o->n_units, per));
-  o->off_part = align_up(4 * int64_t(o->n_panels), kAlign);
+  o->off_part = std::max(kOneCounterBytes, align_up(4 * int64_t(o->n_panels), kAlign));
   o->ws_bytes = o->off_part + 2 * int64_t(o->grid) * o->rp * batch * 4;
   return true;
 }
