@@ -185,7 +185,7 @@ def kernel_name(B, grouped=False, rows_per_panel=1024, e4m3=False, g128=False):
         return f"tern_mfma_kernel<{2 if B <= 4 else 3}, 8, 1, {f8}, true>"
     if B > 1:
         return f"grouped_mma_kernel<2, {f8}, true>"
-    return f"grouped_gemv_kernel<4, {f8}, {'true' if g128 else 'false'}, true>"
+    return f"tern_solo_kernel<{f8}>"
 
 
 def traffic_per_launch(kernel, algorithmic_bytes, workload="llama3_8b_stack batch 1"):

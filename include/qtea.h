@@ -179,11 +179,10 @@ int qtea_pack_g128(const int8_t* trits, int64_t N, int64_t K, const uint16_t* gr
 /*
  * Workspace bytes that qtea_gemv (batch = 1) / qtea_gemm_lowbatch need for
  * this matrix at this batch size on the current device.  A call splits the
- * matrix's output panels (512 rows) and its K range
- * into work units over one launch; a panel whose units fall to more than
- * one workgroup is summed from their partial rows in a fixed order, at
- * batch 1 by the last of them to arrive, at batch 2..16 by a second small
- * kernel on the same stream.  The workspace holds the arrival counters (64 KB,
+ * matrix's output rows and its K range over the workgroups of one launch;
+ * rows whose shares fall to more than one workgroup are summed from their
+ * partial rows in a fixed order, at batch 1 by the last of them to arrive,
+ * at batch 2..16 by a second small kernel on the same stream.  The workspace holds the arrival counters (64 KB,
  * more for a matrix of more than 16384 panels; the same place for every
  * matrix) and two slots of partial rows per workgroup.  It must be zero-filled before its first use
  * (qtea_workspace_init or any zero fill); every call that runs to
@@ -220,9 +219,13 @@ int qtea_gemv(const qtea_desc* desc, const void* packed, const uint16_t* x, floa
  * Y = X W^T for 1 <= batch <= QTEA_MAX_BATCH activation rows (low-batch
  * decode: one token per row).
  *   X  device fp16 [batch][K] row-major;  Y  device fp32 [batch][N] row-major.
- * Batch 1 runs the table-lookup kernel, batch 2..16 the matrix-core kernel
- * (fp16 products of the exact ternary codes with the activations split
- * into two fp16 halves, fp32 accumulation).  Errors as qtea_gemv plus
+ * Batch 1..8 runs the matrix cores on the exact ternary codes in FP4, with the
+ * activations v_j x_j in fixed point, 28 bits to a block of 20 columns, as six
+ * digits; batch 9..16 on the codes in fp16 with the activations split into
+ * two fp16 halves; fp32 accumulation.  (The grouped format, and matrices
+ * too large for the batch-1 form's workspace, run the table-lookup kernel.)
+ * An activation that is not finite makes every output of its row NaN, as
+ * 0 * inf does in the dense product.  Errors as qtea_gemv plus
  * QTEA_ERR_BATCH.
  */
 int qtea_gemm_lowbatch(const qtea_desc* desc, const void* packed, const uint16_t* X, int batch,

@@ -8,7 +8,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SRCS = [os.path.join(HERE, "csrc", f) for f in ("qtea.hip", "grouped.hip", "grouped_mma.hip", "tern_mfma.hip", "quant.hip")]
+SRCS = [os.path.join(HERE, "csrc", f) for f in ("qtea.hip", "grouped.hip", "grouped_mma.hip", "tern_mfma.hip", "tern_solo.hip", "quant.hip")]
 LIB = os.path.join(HERE, "libqtea.so")
 # the debug build: unused byte values 243..255 of every decode table read NaN
 LIB_DEBUG = os.path.join(HERE, "libqtea_debug.so")

@@ -895,8 +895,11 @@ int one_launch(const qtea_desc& d, const void* packed, const uint16_t* X, int ba
   one.n_units = int32_t(o.n_units);
   one.batch = batch;
   hipError_t e;
+  const SoloShape solo = batch == 1 ? solo_shape(d, o, cu_count()) : SoloShape{0, 1, 1};
   if (batch > 1)
     e = launch_one_mma(one, o.grid, f8, part, st);
+  else if (solo.parts > 0)
+    e = launch_solo(one.pr, solo, cu_count(), f8, part, counters, st);
   else if (g128)
     e = launch_one_b1<true, true>(one, o.grid, part, counters, st);
   else

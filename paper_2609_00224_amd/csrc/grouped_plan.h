@@ -127,6 +127,12 @@ constexpr int kOneTernBatch = 8;
 hipError_t launch_grouped_tern(const uint8_t* plan, int grid, bool f8, float* part, hipStream_t st);
 hipError_t launch_one_tern(const GOne& one, int grid, bool f8, float* part, hipStream_t st);
 
+// One problem at batch 1 by tasks (tern_solo.hip; s from solo_shape), over at
+// most max_wg workgroups; part: 64 floats per tile and part, counters: one
+// word per tile (zero on entry and on exit), both unused with one part.
+hipError_t launch_solo(const GProblem& pr, const SoloShape& s, int max_wg, bool f8, float* part, uint32_t* counters,
+                       hipStream_t st);
+
 // The low-batch launches (grouped_mma.hip): a plan of batch 2..16 over `grid`
 // workgroups, and one problem (one.batch rows; split panels summed by a
 // second kernel), each by the kernel that is faster at its batch.

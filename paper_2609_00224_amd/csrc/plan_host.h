@@ -196,6 +196,36 @@ inline bool one_shape_for(const qtea_desc& d, int batch, int max_wg, int rp, One
   return true;
 }
 
+// One matrix at batch 1 through the task kernel (tern_solo.hip): its tasks are
+// the K slices and the salient columns by `chunks` (1..kSoloChunks) times 32,
+// at most kSoloTasks of them per workgroup; a matrix of more is cut in
+// `parts`.  As few parts as the largest residual tasks allow (a second part
+// costs a sum across workgroups), then the smallest residual tasks that keep
+// them.  Where the 64-row tiles leave workgroups idle, a tile is cut in
+// `split` pieces (2 or 4: whole 16-row tiles), as long as every piece has a
+// workgroup of its own.  parts = 0 where that kernel does not run: the
+// grouped format, and matrices whose part sums (64 floats per piece and part)
+// or arrival counters (one per piece) would not fit the workspace that
+// one_shape_for sizes.
+constexpr int kSoloTasks = 16, kSoloChunks = 3;
+struct SoloShape {
+  int parts, chunks, split;
+};
+inline SoloShape solo_shape(const qtea_desc& d, const OneShape& o, int max_wg) {
+  SoloShape s{0, 1, 1};
+  if (d.layout == kLayoutG128 || max_wg < 1) return s;
+  auto tasks = [&](int c) { return cdiv(d.n_groups, kSliceGroups) + cdiv(d.n_salient, 32 * c); };
+  const int64_t parts = cdiv(tasks(kSoloChunks), kSoloTasks), n_tiles = d.n_pad / 64;
+  auto fits = [&](int64_t pieces) {
+    return parts == 1 || (4 * pieces <= o.off_part && 256 * parts * pieces <= o.ws_bytes - o.off_part);
+  };
+  if (!fits(n_tiles)) return s;
+  while (cdiv(tasks(s.chunks), kSoloTasks) > parts) ++s.chunks;
+  while (s.split < 4 && 2 * s.split * n_tiles * parts <= max_wg && fits(2 * s.split * n_tiles)) s.split *= 2;
+  s.parts = int(parts);
+  return s;
+}
+
 // Layout of the plan of n_problems problems for a launch of G workgroups:
 // header, problem records, chunk records from plan_off_chunks, split
 // records from plan_off_splits, plan_bytes_for bytes in all.

@@ -64,28 +64,10 @@
 // position words of the next 32 columns are already in flight.
 #include <type_traits>
 
-#include "grouped_plan.h"
+#include "tern_common.h"
 
 namespace qtea_grouped {
 namespace {
-
-constexpr int kDigits = 6;
-constexpr uint32_t kDigitBias = 0x21084210u;  // 16 * (1 + 32 + ... + 32^5)
-constexpr int kUnitMfma = 4;                  // instructions per 16-row tile, unit and result block
-// Decode table rows of 256 bytes: 32 copies of the entry, and 128 bytes that
-// hold the small per-wave and per-workgroup areas ("holes").  The debug
-// build (QTEA_DEBUG) keeps the rows of the unused byte values 243..255 (zero
-// entries) so that such a byte, which it reports as NaN, reads its own row.
-#ifdef QTEA_DEBUG
-constexpr int kTabRows = 256;
-#else
-constexpr int kTabRows = kCodes;
-#endif
-constexpr int kTab = kTabRows * 256;
-constexpr int kHoleBytes = kCodes * 128;
-// Staging area of a wave and tile: 32 columns' residual values of the tile (1 KiB)
-// and their position words; the part end transposes its sums through it.
-constexpr int kStage = 1024 + 128;
 
 // batch rows of the kernel with NB result blocks, at most
 constexpr int tern_bm(int NB) { return NB == 2 ? 4 : 8; }
@@ -107,68 +89,6 @@ struct TLds {
   static constexpr int RINGB = RING * 64 * BM;
   static_assert(RINGB % 128 == 0 && RINGB + WAVES * TW * kStage <= kHoleBytes, "small areas fit the holes");
 };
-
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-typedef __attribute__((address_space(1))) f32x4u gf32x4u;
-typedef __attribute__((address_space(1))) const u32x2 gu32x2;
-template <class T>
-using lds_t = __attribute__((address_space(3))) T;
-
-template <class T>
-__device__ __forceinline__ T lds_read(uint32_t a) {
-  return *(const lds_t<T>*)(size_t(a));
-}
-template <class T>
-__device__ __forceinline__ void lds_write(uint32_t a, T v) {
-  *(lds_t<T>*)(size_t(a)) = v;
-}
-
-// Address of byte o of the space formed by the unused halves of the table rows.
-__device__ __forceinline__ constexpr uint32_t hole(uint32_t o) { return o + (o & ~127u) + 128u; }
-
-__device__ __forceinline__ half8 as_half8(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-  const u32x4 v = {a, b, c, d};
-  return __builtin_bit_cast(half8, v);
-}
-
-// The five codes of byte value c as FP4 nibbles (digit 0 lowest).
-__device__ __forceinline__ uint32_t tern_entry(uint32_t c) {
-  uint32_t e = 0;
-#pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    const uint32_t r = c / 3, d = c - 3 * r;
-    e |= (d == 0 ? 0xAu : (d == 1 ? 0u : 0x2u)) << (4 * i);
-    c = r;
-  }
-  return e;
-}
-
-// One instruction: digits (FP6) x codes (FP4) with the digits' block scales
-// in byte I of sc.
-template <int I>
-__device__ __forceinline__ f32x4 tern_mfma(const u32x4 a, const u32x2 a2, const uint32_t (&e)[4], const f32x4 c,
-                                           const uint32_t sc) {
-  const i32x8 A = {int(a.x), int(a.y), int(a.z), int(a.w), int(a2.x), int(a2.y), 0, 0};
-  const i32x8 B = {int(e[0]), int(e[1]), int(e[2]), int(e[3]), 0, 0, 0, 0};
-  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(A, B, c, 2, 4, I, int(sc), 0, 0x7f7f7f7f);
-}
-
-// Max over the four lanes of a quad.
-__device__ __forceinline__ uint32_t quad_max(uint32_t x) {
-  const uint32_t y = max(x, uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0xB1, 0xf, 0xf, true)));   // 1,0,3,2
-  return max(y, uint32_t(__builtin_amdgcn_update_dpp(0, int(y), 0x4E, 0xf, 0xf, true)));               // 2,3,0,1
-}
-
-// The lane index, opaque: what is derived from it is computed where it is
-// used instead of being held in registers across the unit loop.
-__device__ __forceinline__ int fresh(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
-}
 
 // F8: residual values are E4M3 bytes (layout 3), else fp16 (layout 2).
 // ONE: a single problem launched on its own (GOne, no plan and no queue):
@@ -274,38 +194,16 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void tern_mfma_kernel(const 
     const uint32_t pi = uint32_t(lane >> 2) & 3u, pp = uint32_t(lane) & 3u;  // instruction and dword group of the pack
     const uint32_t img = uint32_t(L::IMG + bb * L::IMGB), img2 = img + uint32_t(L::IMG1);
     const uint32_t sc = uint32_t(L::SC + bb * NB * 256);
-    float a[5];
-    uint32_t mx = 0;
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-      a[i] = float(__builtin_bit_cast(_Float16, uint16_t(vr[i] & 0xffffu))) * float(__builtin_bit_cast(_Float16, xr[i]));
-      mx = max(mx, __builtin_bit_cast(uint32_t, a[i]) & 0x7fffffffu);
-    }
-    mx = quad_max(mx);
-    const uint32_t ex = max(mx >> 23, 64u);  // |a| >= 2^-48 unless zero
-    const float scale = __builtin_bit_cast(float, (281u - ex) << 23);  // |a| scale < 2^28
-    uint32_t uq[5];
-#pragma unroll
-    for (int i = 0; i < 5; ++i) uq[i] = uint32_t(int(__builtin_rintf(a[i] * scale))) + kDigitBias;
+    uint32_t P[kDigits], ex, mx;
+    tern_digits(vr, xr, P, ex, mx);
     // A quad of lanes holds the four packs of one instruction, column group
     // and digit: 30-bit codes at bits 0, 48, 96, 144 of the operand.  Its
     // first lane writes the first four dwords, its last lane the other two.
-    uint32_t P[kDigits], P1[kDigits], P2[kDigits];
+    uint32_t P1[kDigits], P2[kDigits];
 #pragma unroll
     for (int l = 0; l < kDigits; ++l) {
-      uint32_t F = 0;  // per column the digit + 16 at bits 6 i .. 6 i + 4
-#pragma unroll
-      for (int i = 0; i < 5; ++i) {
-        const uint32_t sh = 6 * i >= 5 * l ? uq[i] << (6 * i - 5 * l) : uq[i] >> (5 * l - 6 * i);
-        F |= sh & (31u << (6 * i));
-      }
-      // to sign (bit 6 i + 5) and magnitude 0..16
-      constexpr uint32_t kOnes = 0x01041041u;
-      const uint32_t s = ~(F >> 4) & kOnes;
-      F = ((F & (15u * kOnes)) ^ ((s << 4) - s)) + (s + (s << 5));
-      P[l] = F;
-      P1[l] = uint32_t(__builtin_amdgcn_update_dpp(0, int(F), 0xF9, 0xf, 0xf, true));  // lane 0: lane 1's
-      P2[l] = uint32_t(__builtin_amdgcn_update_dpp(0, int(F), 0xFE, 0xf, 0xf, true));  // lane 0: lane 2's
+      P1[l] = quad_next(P[l]);
+      P2[l] = quad_next2(P[l]);
     }
     // operand record of result row (b, l)
     auto record = [&](int l, uint32_t& nb, uint32_t& m) -> uint32_t {
@@ -320,8 +218,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void tern_mfma_kernel(const 
         uint32_t nb, m;
         const uint32_t rec = record(l, nb, m);
         lds_write<u32x4>(img + rec * 16u, u32x4{P[l], P1[l] << 16, P1[l] >> 16, P2[l]});
-        const uint32_t e = mx >= 0x7f800000u ? 255u : ex + 5u * uint32_t(l) - 24u;
-        lds_write<uint8_t>(sc + (nb * 64u + m + 16u * uint32_t(kg)) * 4u + pi, uint8_t(e));
+        lds_write<uint8_t>(sc + (nb * 64u + m + 16u * uint32_t(kg)) * 4u + pi, tern_scale(ex, mx, l));
       }
     }
     if (pp == 3u) {
