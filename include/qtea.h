@@ -21,7 +21,8 @@
  * Conventions for every entry point:
  *   - All pointers named "device" are HIP device pointers owned by the
  *     caller.  The library never allocates or frees memory and keeps no
- *     global state; every entry point is reentrant.
+ *     global state but a device's workgroup counts, asked for once; every
+ *     entry point is reentrant.
  *   - `stream` is a hipStream_t (NULL = the null stream).  Device work is
  *     enqueued on it and is stream-ordered with the caller's other work.
  *     Only qtea_pack synchronizes the stream (to return its validation

@@ -37,6 +37,7 @@
 #include <stdlib.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <vector>
 
@@ -829,25 +830,44 @@ hipError_t set_lds_attr() {
   return hipSuccess;
 }
 
-int cu_count() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+// A device's workgroup counts do not change: each is asked for once per device
+// (the occupancy query alone took longer than the rest of a call's host work).
+constexpr int kMaxDevices = 64;
+template <class Query>
+int per_device(std::atomic<int> (&known)[kMaxDevices], Query query) {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
+  if (dev >= kMaxDevices) return query(dev);
+  int n = known[dev].load(std::memory_order_relaxed);
+  if (n == 0) {
+    n = query(dev);  // (0 on failure: asked for again next time)
+    known[dev].store(n, std::memory_order_relaxed);
+  }
   return n;
+}
+
+int cu_count() {
+  static std::atomic<int> known[kMaxDevices];
+  return per_device(known, [](int dev) {
+    int n = 0;
+    return hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 0;
+  });
 }
 
 // Workgroups of the launch: kWgPerCu per CU when that many fit (they do on
 // gfx950: 160 KB of LDS, 16 waves of at most 128 VGPRs), else one per CU.
 // The kernel never waits for another workgroup, so any grid is correct.
 int grid_size() {
-  int dev = 0, n = 0, per = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  if (set_lds_attr<kMaxRB, false>() != hipSuccess) return 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(&grouped_gemv_kernel<kMaxRB, false>),
-                                                   kGT, GLds<kMaxRB>::BYTES) != hipSuccess)
-    return 0;
-  return n * std::max(1, std::min(per, kWgPerCu));
+  static std::atomic<int> known[kMaxDevices];
+  return per_device(known, [](int) {
+    const int n = cu_count();
+    int per = 0;
+    if (n < 1 || set_lds_attr<kMaxRB, false>() != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(&grouped_gemv_kernel<kMaxRB, false>),
+                                                     kGT, GLds<kMaxRB>::BYTES) != hipSuccess)
+      return 0;
+    return n * std::max(1, std::min(per, kWgPerCu));
+  });
 }
 
 template <int RB, bool F8, bool G128 = false>
@@ -918,7 +938,6 @@ int one_launch(const qtea_desc& d, const void* packed, const uint16_t* X, int ba
 // completes), then the partial rows.
 constexpr int64_t kNoallocCounterBytes = 65536;
 static __device__ __align__(256) uint8_t scratch[QTEA_NOALLOC_SCRATCH_BYTES];
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[kMaxDevices] = {};
 
