@@ -128,64 +128,81 @@ __device__ inline int tern(double x, double thr) { return x > thr ? 1 : (x < -th
 // ---------------------------------------------------------------------------
 // Hessian and salient columns.
 // ---------------------------------------------------------------------------
+// H = scale X^T X: a tile of 64 x 64 outputs per workgroup, four waves of 32 x
+// 32 each on the fp64 matrix cores, which add the four products of a step one
+// after another in ascending row order, each rounded: H has the bits of a loop
+// of fused multiply-adds.  Tiles below the diagonal leave, the others write
+// both halves.  Bound by the matrix cores' fp64 rate, which is the vector
+// units': the gain is in LDS reads, four per four steps of 16 x 16 x 4 where a
+// thread's 8 x 8 outputs took sixteen per row and kept LDS as busy as the
+// multiply-adds, and in tiles small enough to spread evenly (528 tiles of 128
+// x 128 ran in two rounds, the second nearly empty).  8192 rows of 4096
+// columns: 7.6 -> 4.0 ms (35 TFLOP/s); 2048 of 14336: 18.6 -> 9.2 ms.  Tiles of
+// 128 x 64 took 4.9 ms, 64 x 128 6.5, 128 x 128 5.7.
+typedef double double4_t __attribute__((ext_vector_type(4)));
+constexpr int kHT = 64;  // rows and columns of a tile
+constexpr int kHR = 32;  // calibration rows staged at a time
 __global__ __launch_bounds__(256) void hess_kernel(const float* __restrict__ X, int64_t n, int64_t K, double scale,
                                                    double* __restrict__ H) {
-  // 128 x 128 output tile, 8 x 8 per thread, calibration rows staged 16 at a
-  // time; tiles on and above the diagonal, each written to its mirror too
-  // (fp64 multiply-adds bound this: 8192 rows of 4096 columns 9.0 -> 7.6 ms)
-  if (blockIdx.x < blockIdx.y) return;
-  __shared__ double xa[16][129], xb[16][129];
-  const int64_t a0 = int64_t(blockIdx.y) * 128, b0 = int64_t(blockIdx.x) * 128;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  double acc[8][8];
+  constexpr int L = kHR * kHT / 256;
+  const int64_t a0 = int64_t(blockIdx.y) * kHT, b0 = int64_t(blockIdx.x) * kHT;
+  if (b0 < a0) return;
+  // (a row's 16 words of padding put the four rows of a step on different banks)
+  __shared__ float xa[kHR][kHT + 16], xb[kHR][kHT + 16];
+  const int lane = threadIdx.x & 63, m = lane & 15, kq = lane >> 4;
+  const int wr = int(threadIdx.x >> 7) * 32, wc = int(threadIdx.x >> 6 & 1) * 32;
+  float ra[L], rb[L];
+  const auto load = [&](int64_t t0) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < L; ++i) {
+      const int e = i * 256 + int(threadIdx.x), c = e % kHT;
+      const int64_t t = t0 + e / kHT;
+      ra[i] = t < n && a0 + c < K ? X[t * K + a0 + c] : 0.0f;
+      rb[i] = t < n && b0 + c < K ? X[t * K + b0 + c] : 0.0f;
+    }
+  };
+  double4_t acc[2][2];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = 0.0;
-  for (int64_t t0 = 0; t0 < n; t0 += 16) {
-    for (int e = threadIdx.x; e < 16 * 128; e += 256) {
-      const int tt = e >> 7, c = e & 127;
-      const int64_t t = t0 + tt;
-      xa[tt][c] = (t < n && a0 + c < K) ? double(X[t * K + a0 + c]) : 0.0;
-      xb[tt][c] = (t < n && b0 + c < K) ? double(X[t * K + b0 + c]) : 0.0;
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = double4_t{0.0, 0.0, 0.0, 0.0};
+  load(0);
+  for (int64_t t0 = 0; t0 < n; t0 += kHR) {
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const int e = i * 256 + int(threadIdx.x);
+      xa[e / kHT][e % kHT] = ra[i];
+      xb[e / kHT][e % kHT] = rb[i];
     }
     __syncthreads();
-    for (int tt = 0; tt < 16; ++tt) {
-      double va[8], vb[8];
+    if (t0 + kHR < n) load(t0 + kHR);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        va[i] = xa[tt][ty + 16 * i];
-        vb[i] = xb[tt][tx + 16 * i];
+    for (int k = 0; k < kHR; k += 4) {
+      double va[2], vb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) va[i] = double(xa[k + kq][wr + 16 * i + m]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) vb[j] = double(xb[k + kq][wc + 16 * j + m]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[i], vb[j], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t a = a0 + wr + 16 * i + 4 * e + kq, b = b0 + wc + 16 * j + m;
+        if (a > b || b >= K) continue;
+        const double h = scale * acc[i][j][e];
+        H[a * K + b] = h;
+        if (a < b) H[b * K + a] = h;
       }
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = fma(va[i], vb[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int64_t a = a0 + ty + 16 * i, b = b0 + tx + 16 * j;
-      if (a < K && b < K) H[a * K + b] = scale * acc[i][j];
-    }
-  if (a0 == b0) return;
-  // H[b][a], sixteen of the tile's columns at a time through LDS (the staging
-  // loop ended with a barrier)
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) xa[tx][ty + 16 * i] = scale * acc[i][j];
-    __syncthreads();
-    for (int e = threadIdx.x; e < 16 * 128; e += 256) {
-      const int cc = e >> 7, rr = e & 127;
-      const int64_t b = b0 + 16 * j + cc, a = a0 + rr;
-      if (b < K && a < K) H[b * K + a] = xa[cc][rr];
-    }
-    __syncthreads();
-  }
 }
 
 __global__ void fill_f64_kernel(double* __restrict__ p, int64_t n, double v) {
@@ -1052,7 +1069,7 @@ extern "C" {
 
 int qtea_quant_hessian(const float* X, int64_t n, int64_t K, double* H, void* stream) {
   if (!X || !H || n < 1 || K < 1 || K > kQMaxCols) return QTEA_ERR_INVALID_ARG;
-  const int64_t T = q_cdiv(K, 128);
+  const int64_t T = q_cdiv(K, kHT);
   if (T > 65535) return QTEA_ERR_INVALID_ARG;
   hipLaunchKernelGGL(hess_kernel, dim3(uint32_t(T), uint32_t(T)), dim3(256), 0, static_cast<hipStream_t>(stream), X,
                      n, K, 2.0 / double(n), H);
