@@ -128,6 +128,30 @@ __device__ inline int tern(double x, double thr) { return x > thr ? 1 : (x < -th
 // ---------------------------------------------------------------------------
 // Hessian and salient columns.
 // ---------------------------------------------------------------------------
+// A wave's 32 x 32 outputs += the products of kc (a multiple of 4) terms on the
+// fp64 matrix cores, a(row, k) and b(column, k) read from LDS: added one after
+// another in ascending k, each rounded, as a loop of fused multiply-adds would.
+// Element e of acc[i][j] is row 16 i + 4 e + lane / 16, column 16 j + lane % 16.
+typedef double double4_t __attribute__((ext_vector_type(4)));
+template <int kc, class FA, class FB>
+__device__ __forceinline__ void mma_f64_32x32(FA a, FB b, double4_t (&acc)[2][2]) {
+  const int lane = threadIdx.x & 63, m = lane & 15, kq = lane >> 4;
+#pragma unroll
+  for (int k = 0; k < kc; k += 4) {
+    double va[2], vb[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      va[i] = a(16 * i + m, k + kq);
+      vb[i] = b(16 * i + m, k + kq);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[i], vb[j], acc[i][j], 0, 0, 0);
+  }
+}
+
 // H = scale X^T X: a tile of 64 x 64 outputs per workgroup, four waves of 32 x
 // 32 each on the fp64 matrix cores, which add the four products of a step one
 // after another in ascending row order, each rounded: H has the bits of a loop
@@ -139,7 +163,6 @@ __device__ inline int tern(double x, double thr) { return x > thr ? 1 : (x < -th
 // x 128 ran in two rounds, the second nearly empty).  8192 rows of 4096
 // columns: 7.6 -> 4.0 ms (35 TFLOP/s); 2048 of 14336: 18.6 -> 9.2 ms.  Tiles of
 // 128 x 64 took 4.9 ms, 64 x 128 6.5, 128 x 128 5.7.
-typedef double double4_t __attribute__((ext_vector_type(4)));
 constexpr int kHT = 64;  // rows and columns of a tile
 constexpr int kHR = 32;  // calibration rows staged at a time
 __global__ __launch_bounds__(256) void hess_kernel(const float* __restrict__ X, int64_t n, int64_t K, double scale,
@@ -176,19 +199,8 @@ __global__ __launch_bounds__(256) void hess_kernel(const float* __restrict__ X, 
     }
     __syncthreads();
     if (t0 + kHR < n) load(t0 + kHR);
-#pragma unroll
-    for (int k = 0; k < kHR; k += 4) {
-      double va[2], vb[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) va[i] = double(xa[k + kq][wr + 16 * i + m]);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) vb[j] = double(xb[k + kq][wc + 16 * j + m]);
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[i], vb[j], acc[i][j], 0, 0, 0);
-    }
+    mma_f64_32x32<kHR>([&](int r, int k) { return double(xa[k][wr + r]); },
+                       [&](int c, int k) { return double(xb[k][wc + c]); }, acc);
     __syncthreads();
   }
 #pragma unroll
@@ -387,47 +399,43 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ A,
 }
 
 // upper triangle of the leading c0 x c0 block -= panel panel^T (the block's
-// 64 columns): 128 x 128 tiles, 8 x 8 outputs per thread (16 LDS reads per
-// 64 products), the panel staged 32 columns at a time
+// 64 columns): 64 x 64 tiles, 32 x 32 outputs per wave on the matrix cores,
+// the panel staged 32 columns at a time
+// (vector multiply-adds on 128 x 128 tiles left most of the chip idle as the
+// leading block shrinks; with trail_gemm_kernel's change the quantization of 4096 x
+// 4096 went from 32.2 to 30.6 ms, of 4096 x 14336 from 241.5 to 223)
 __global__ __launch_bounds__(256) void chol_trail_kernel(double* __restrict__ A, int64_t K, int64_t c0) {
   const int64_t tp = blockIdx.y, tq = blockIdx.x;
   if (tp > tq) return;
-  __shared__ double Pp[kNBH][129], Pq[kNBH][129];  // [k][row of the tile]
-  const int64_t p0 = tp * 128, q0 = tq * 128;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  double acc[8][8];
+  __shared__ double Pp[64][kNBH + 2], Pq[64][kNBH + 2];  // [row of the tile][k]
+  const int64_t p0 = tp * 64, q0 = tq * 64;
+  const int lane = threadIdx.x & 63, m = lane & 15, kq = lane >> 4;
+  const int wr = int(threadIdx.x >> 7) * 32, wc = int(threadIdx.x >> 6 & 1) * 32;
+  double4_t acc[2][2];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = 0.0;
+    for (int j = 0; j < 2; ++j) acc[i][j] = double4_t{0.0, 0.0, 0.0, 0.0};
   for (int h = 0; h < kNB; h += kNBH) {
-    for (int e = threadIdx.x; e < 128 * kNBH; e += 256) {
-      const int i = e / kNBH, k = e % kNBH;
-      Pp[k][i] = p0 + i < c0 ? A[(p0 + i) * K + c0 + h + k] : 0.0;
-      Pq[k][i] = q0 + i < c0 ? A[(q0 + i) * K + c0 + h + k] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 64 * kNBH / 256; ++u) {
+      const int e = u * 256 + int(threadIdx.x), i = e / kNBH, k = e % kNBH;
+      Pp[i][k] = p0 + i < c0 ? A[(p0 + i) * K + c0 + h + k] : 0.0;
+      Pq[i][k] = q0 + i < c0 ? A[(q0 + i) * K + c0 + h + k] : 0.0;
     }
     __syncthreads();
-    for (int k = 0; k < kNBH; ++k) {
-      double va[8], vb[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        va[i] = Pp[k][ty + 16 * i];
-        vb[i] = Pq[k][tx + 16 * i];
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = fma(va[i], vb[j], acc[i][j]);
-    }
+    mma_f64_32x32<kNBH>([&](int r, int k) { return Pp[wr + r][k]; }, [&](int c, int k) { return Pq[wc + c][k]; }, acc);
     __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int64_t p = p0 + ty + 16 * i, q = q0 + tx + 16 * j;
-      if (p < c0 && q < c0 && p <= q) A[p * K + q] -= acc[i][j];
-    }
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t p = p0 + wr + 16 * i + 4 * e + kq, q = q0 + wc + 16 * j + m;
+        if (q < c0 && p <= q) A[p * K + q] -= acc[i][j][e];
+      }
 }
 
 // U = V^-1 by recursive doubling: the 64 x 64 diagonal blocks (from the
@@ -1018,47 +1026,42 @@ __global__ __launch_bounds__(kCBWaves * 64, 4) void col_block_kernel(ColBlockArg
   }
 }
 
-// Wt[k][r] -= sum_{i < B} U[b0 + i][k] Et[i][r] for k in [b1, K)
+// Wt[k][r] -= sum_{i < B} U[b0 + i][k] Et[i][r] for k in [b1, K), tiles of 64 x 64
+// on the matrix cores (four LDS reads per four 16 x 16 x 4 products, eight per 16
+// multiply-adds of each thread before: figures at chol_trail_kernel)
 __global__ __launch_bounds__(256) void trail_gemm_kernel(double* __restrict__ Wt, const double* __restrict__ U,
                                                          const double* __restrict__ Et, int64_t N, int64_t K,
                                                          int64_t b0, int64_t B, int64_t b1) {
-  __shared__ double Us[32][65], Es[32][65];
+  __shared__ double Us[32][64 + 16], Es[32][64 + 16];  // (two rows of a step on different banks)
   const int64_t r0 = int64_t(blockIdx.x) * 64, k0 = b1 + int64_t(blockIdx.y) * 64;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  double acc[4][4];
+  const int lane = threadIdx.x & 63, m = lane & 15, kq = lane >> 4;
+  const int wr = int(threadIdx.x >> 7) * 32, wc = int(threadIdx.x >> 6 & 1) * 32;
+  double4_t acc[2][2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.0;
+    for (int j = 0; j < 2; ++j) acc[i][j] = double4_t{0.0, 0.0, 0.0, 0.0};
   for (int64_t i0 = 0; i0 < B; i0 += 32) {
-    for (int e = threadIdx.x; e < 32 * 64; e += 256) {
-      const int ii = e >> 6, c = e & 63;
+#pragma unroll
+    for (int u = 0; u < 32 * 64 / 256; ++u) {
+      const int e = u * 256 + int(threadIdx.x), ii = e >> 6, c = e & 63;
       const bool in = i0 + ii < B;
       Us[ii][c] = (in && k0 + c < K) ? U[(b0 + i0 + ii) * K + k0 + c] : 0.0;
       Es[ii][c] = (in && r0 + c < N) ? Et[(i0 + ii) * N + r0 + c] : 0.0;
     }
     __syncthreads();
-    for (int ii = 0; ii < 32; ++ii) {
-      double uk[4], er[4];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        uk[m] = Us[ii][ty + 16 * m];
-        er[m] = Es[ii][tx + 16 * m];
-      }
-#pragma unroll
-      for (int m = 0; m < 4; ++m)
-#pragma unroll
-        for (int n = 0; n < 4; ++n) acc[m][n] = fma(uk[m], er[n], acc[m][n]);
-    }
+    mma_f64_32x32<32>([&](int r, int k) { return Us[k][wr + r]; }, [&](int c, int k) { return Es[k][wc + c]; }, acc);
     __syncthreads();
   }
 #pragma unroll
-  for (int m = 0; m < 4; ++m)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int n = 0; n < 4; ++n) {
-      const int64_t k = k0 + ty + 16 * m, r = r0 + tx + 16 * n;
-      if (k < K && r < N) Wt[k * N + r] -= acc[m][n];
-    }
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t k = k0 + wr + 16 * i + 4 * e + kq, r = r0 + wc + 16 * j + m;
+        if (k < K && r < N) Wt[k * N + r] -= acc[i][j][e];
+      }
 }
 
 int grid1(int64_t n, int per) { return int(q_cdiv(n, per) < 65535 * 16 ? q_cdiv(n, per) : 65535 * 16); }
@@ -1134,7 +1137,7 @@ int qtea_quantize(const double* W, const double* H, int64_t N, int64_t K, const 
     hipLaunchKernelGGL(chol_diag_kernel, dim3(1), dim3(256), 0, st, A, K, lo, int(hi - lo), status);
     if (lo > 0) {
       hipLaunchKernelGGL(chol_panel_kernel, dim3(uint32_t(q_cdiv(lo, 256))), dim3(256), 0, st, A, K, lo);
-      const int64_t tl = q_cdiv(lo, 128);
+      const int64_t tl = q_cdiv(lo, 64);
       hipLaunchKernelGGL(chol_trail_kernel, dim3(uint32_t(tl), uint32_t(tl)), dim3(256), 0, st, A, K, lo);
     }
   }
