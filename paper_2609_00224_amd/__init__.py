@@ -1,8 +1,8 @@
 """MI355X (gfx950) compressed ternary GEMV: Python binding of libqtea.so.
 
 The binding marshals arguments only: every step of the GEMV runs in the HIP
-kernels of ``csrc/qtea.hip``, ``csrc/grouped.hip`` and ``csrc/grouped_mma.hip``
-behind the C ABI of ``include/qtea.h``, and every step of the offline
+kernels of ``csrc/qtea.hip``, ``csrc/grouped.hip``, ``csrc/grouped_mma.hip``,
+``csrc/tern_mfma.hip`` and ``csrc/tern_solo.hip`` behind the C ABI of ``include/qtea.h``, and every step of the offline
 quantizer in those of ``csrc/quant.hip`` behind ``include/qtea_quant.h``.  Torch
 is used to allocate device memory and to name the current HIP stream.
 There is no CPU fallback: if the library is not built, loading it raises.
