@@ -805,10 +805,17 @@ __global__ __launch_bounds__(kCT) void col_kernel(ColArgs a) {
 // Every wait ends: the workgroups are few enough to be resident together,
 // and a wait that lasts 20 s all the same (more such kernels at once than the
 // device holds) raises status[1], after which this and the following
-// launches return at once and the call reports an error.
+// launches return at once and the call quantizes the columns again by the
+// launches per column.
 // ---------------------------------------------------------------------------
 constexpr int kCBWaves = kQG / kColChunk;  // 8
+#ifdef QTEA_DEBUG
+// the debug build's waits run out at the second look, which takes its calls
+// of more than one workgroup through the launches per column
+constexpr uint64_t kXchTicks = 0;
+#else
 constexpr uint64_t kXchTicks = 2000000000ull;  // 20 s of the 100 MHz counter
+#endif
 
 struct ColBlockArgs {
   const double* Wt;
@@ -857,7 +864,6 @@ __global__ __launch_bounds__(kCBWaves * 64, 4) void col_block_kernel(ColBlockArg
   // per wave 16 x 16 values of U: rows of a chunk of columns, its own columns
   __shared__ double us[kCBWaves][kColChunk][kColChunk];
   __shared__ int stop_s;
-  if (a.status[1] != 0) return;  // (written before this launch only)
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nwg = gridDim.x;
   const int64_t r = int64_t(blockIdx.x) * 64 + lane;
@@ -865,7 +871,7 @@ __global__ __launch_bounds__(kCBWaves * 64, 4) void col_block_kernel(ColBlockArg
   const int nb = int(a.b1 - a.b0);
   const double al = live ? f16_to_f64(a.alpha[r * a.G + a.g]) : 1.0;
   const double be = live ? f16_to_f64(a.beta[r * a.G + a.g]) : 0.0;
-  if (threadIdx.x == 0) stop_s = 0;
+  if (threadIdx.x == 0) stop_s = a.status[1];
   double w[kColChunk];
 #pragma unroll
   for (int m = 0; m < kColChunk; ++m) {
@@ -892,6 +898,8 @@ __global__ __launch_bounds__(kCBWaves * 64, 4) void col_block_kernel(ColBlockArg
   const double gu = exp((-a.lambda * (du / a.dmean[a.g])) * (double(mc) / double(nb)));
   double own[4];
   load_u(wv, own);  // rows and columns of the wave's own chunk
+  __syncthreads();
+  if (stop_s) return;
   auto lane_double = [&](double x, int l) -> double {  // l: uniform
     const uint64_t b = uint64_t(__double_as_longlong(x));
     const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(b)), l));
@@ -1151,8 +1159,6 @@ int qtea_quantize(const double* W, const double* H, int64_t N, int64_t K, const 
   }
   hipLaunchKernelGGL(dmean_kernel, dim3(uint32_t(q_cdiv(G, 256))), dim3(256), 0, st, U, K, dmean);
   // 3. columns
-  hipLaunchKernelGGL(transpose_kernel, dim3(uint32_t(q_cdiv(K, 32)), uint32_t(q_cdiv(N, 32))), dim3(256), 0, st, W,
-                     N, K, H, Wt);
   ColArgs a{};
   a.Wt = Wt;
   a.U = U;
@@ -1172,11 +1178,7 @@ int qtea_quantize(const double* W, const double* H, int64_t N, int64_t K, const 
   a.nwg = nwg;
   a.iters = p->iters;
   a.lambda = p->lambda_decay;
-  const bool in_block = nwg <= kXchWgs;
   unsigned long long* xch = reinterpret_cast<unsigned long long*>(ws + L.xch);
-  uint32_t seq = 0;
-  if (in_block)
-    hipLaunchKernelGGL(fill_f64_kernel, dim3(4), dim3(256), 0, st, reinterpret_cast<double*>(xch), int64_t(2 * kXchWgs * 4), 0.0);
   int s = 0;  // partials / previous-v buffer the next stage reads
   auto stage = [&](int mode) {
     a.part_in = part + s * nwg * 2;
@@ -1193,38 +1195,53 @@ int qtea_quantize(const double* W, const double* H, int64_t N, int64_t K, const 
     }
     s ^= 1;
   };
-  for (int64_t g = 0; g < G; ++g) {
-    const int64_t b0 = g * kQG, b1 = b0 + kQG < K ? b0 + kQG : K;
-    hipLaunchKernelGGL(group_params_kernel, dim3(uint32_t(nwg)), dim3(kCT), 0, st, Wt, N, K, G, g, group_scale,
-                       group_bias);
-    a.g = g;
-    a.b0 = b0;
-    a.b1 = b1;
-    if (in_block) {
-      const ColBlockArgs cb{Wt,   U,   dmean, group_scale, group_bias, rank, Et, T, Q,  col_rescale, resid_val,
-                            resid_idx, xch, status, N,     K,          G,    g,  b0, b1, seq,        p->iters,
-                            p->lambda_decay};
-      hipLaunchKernelGGL(col_block_kernel, dim3(uint32_t(nwg)), dim3(kCBWaves * 64), 0, st, cb);
-      seq += uint32_t(b1 - b0) * uint32_t(p->iters);
-    } else {
-      a.j = b0;
-      if (p->iters > 0) stage(kStart);
-      for (int64_t j = b0; j < b1; ++j) {
-        a.j = j;
-        for (int it = 1; it < p->iters; ++it) stage(kRefine);
-        stage(kFinal);
+  auto columns = [&](bool in_block) {
+    hipLaunchKernelGGL(transpose_kernel, dim3(uint32_t(q_cdiv(K, 32)), uint32_t(q_cdiv(N, 32))), dim3(256), 0, st, W,
+                       N, K, H, Wt);
+    uint32_t seq = 0;
+    if (in_block)
+      hipLaunchKernelGGL(fill_f64_kernel, dim3(4), dim3(256), 0, st, reinterpret_cast<double*>(xch),
+                         int64_t(2 * kXchWgs * 4), 0.0);
+    for (int64_t g = 0; g < G; ++g) {
+      const int64_t b0 = g * kQG, b1 = b0 + kQG < K ? b0 + kQG : K;
+      hipLaunchKernelGGL(group_params_kernel, dim3(uint32_t(nwg)), dim3(kCT), 0, st, Wt, N, K, G, g, group_scale,
+                         group_bias);
+      a.g = g;
+      a.b0 = b0;
+      a.b1 = b1;
+      if (in_block) {
+        const ColBlockArgs cb{Wt,   U,   dmean, group_scale, group_bias, rank, Et, T, Q,  col_rescale, resid_val,
+                              resid_idx, xch, status, N,     K,          G,    g,  b0, b1, seq,        p->iters,
+                              p->lambda_decay};
+        hipLaunchKernelGGL(col_block_kernel, dim3(uint32_t(nwg)), dim3(kCBWaves * 64), 0, st, cb);
+        seq += uint32_t(b1 - b0) * uint32_t(p->iters);
+      } else {
+        a.j = b0;
+        if (p->iters > 0) stage(kStart);
+        for (int64_t j = b0; j < b1; ++j) {
+          a.j = j;
+          for (int it = 1; it < p->iters; ++it) stage(kRefine);
+          stage(kFinal);
+        }
       }
+      if (b1 < K)
+        hipLaunchKernelGGL(trail_gemm_kernel, dim3(uint32_t(q_cdiv(N, 64)), uint32_t(q_cdiv(K - b1, 64))), dim3(256), 0,
+                           st, Wt, U, Et, N, K, b0, b1 - b0, b1);
     }
-    if (b1 < K)
-      hipLaunchKernelGGL(trail_gemm_kernel, dim3(uint32_t(q_cdiv(N, 64)), uint32_t(q_cdiv(K - b1, 64))), dim3(256), 0,
-                         st, Wt, U, Et, N, K, b0, b1 - b0, b1);
-  }
-  if (hipGetLastError() != hipSuccess) return QTEA_ERR_HIP;
-  if (hipStreamSynchronize(st) != hipSuccess) return QTEA_ERR_HIP;
+  };
   int32_t host_status[2] = {0, 0};
-  if (hipMemcpy(host_status, status, sizeof(host_status), hipMemcpyDeviceToHost) != hipSuccess) return QTEA_ERR_HIP;
+  auto finish = [&]() -> bool {
+    return hipGetLastError() == hipSuccess && hipStreamSynchronize(st) == hipSuccess &&
+           hipMemcpy(host_status, status, sizeof(host_status), hipMemcpyDeviceToHost) == hipSuccess;
+  };
+  columns(nwg <= kXchWgs);
+  if (!finish()) return QTEA_ERR_HIP;
   if (host_status[0]) return QTEA_ERR_NOT_POSITIVE;
-  return host_status[1] ? QTEA_ERR_HIP : QTEA_OK;
+  if (host_status[1]) {  // the workgroups were not resident together: the launches per column need no exchange
+    columns(false);
+    if (!finish()) return QTEA_ERR_HIP;
+  }
+  return QTEA_OK;
 }
 
 }  // extern "C"

@@ -38,6 +38,29 @@ def test_column_phase_matches_oracle(N, K, nS, iters):
     assert np.array_equal(got["R8"], ref["rval"]) and np.array_equal(got["idx"], ref["ridx"])
 
 
+@pytest.mark.parametrize("N,K,nS,iters", [(8192, 140, 3, 2), (132, 300, 4, 3)])
+def test_columns_again_when_an_exchange_runs_out(N, K, nS, iters):
+    """The debug build's waits between workgroups run out at once: its call
+    quantizes the columns again by the launches per column and gives the
+    release build's bits."""
+    import torch
+
+    import paper_2609_00224_amd as q
+
+    print(f"[case] quantize again {N}x{K}, {nS} salient, {iters} rounds", flush=True)
+    W, X = synth.quant_inputs(300 + K, N, K, 3 * K)
+    W, H = torch.from_numpy(W).to("cuda"), torch.from_numpy(qz.hessian(X)).to("cuda")
+    want = q.quantize_matrix(W, H, nS, iters=iters)
+    saved = q._lib
+    q._lib = q.open_library(q.DEBUG_LIB_PATH)
+    try:
+        got = q.quantize_matrix(W, H, nS, iters=iters)
+    finally:
+        q._lib = saved
+    for k, v in want.items():
+        assert v is None or torch.equal(v, got[k]), k
+
+
 @pytest.mark.parametrize("K", [1, 127, 128, 129, 300])
 def test_hessian_tiles_symmetric(K):
     """Every product is exact in 64 bits and both orders of a pair are summed
