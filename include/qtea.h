@@ -166,9 +166,8 @@ int qtea_pack_e4m3(const int8_t* trits, int64_t N, int64_t K, const uint16_t* ro
  * A matrix in this layout runs through the batch-1 table kernel (the per-
  * group scale and bias are applied as each group's table sums are added):
  * at batch B, qtea_gemm_lowbatch and the grouped entry points run the B
- * activation rows one after another (B batch-1 launches, or B batch-1
- * problems in one grouped launch), so its weights are streamed once per
- * row.  qtea_debug_unpack returns its codes as [N][26 ceil(K/128)], group
+ * activation rows as B batch-1 problems of one launch, so its weights are
+ * streamed once per row.  qtea_workspace_bytes is the same at every batch.  qtea_debug_unpack returns its codes as [N][26 ceil(K/128)], group
  * after group.
  */
 int qtea_packed_bytes_g128(int64_t N, int64_t K, int64_t n_salient, int64_t* out_bytes);

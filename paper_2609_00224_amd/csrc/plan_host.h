@@ -66,7 +66,8 @@ struct GOne {
   GProblem pr;
   int32_t n_units;
   int32_t batch;
-  int32_t reserved[2];
+  int32_t x_stride;  // table kernel: activations from one batch row (blockIdx.y) to the next
+  int32_t reserved;
 };
 
 // Workgroup whose run holds unit x, for U units over G runs: the largest g
@@ -193,6 +194,20 @@ inline bool one_shape_for(const qtea_desc& d, int batch, int max_wg, int rp, One
   o->grid = int(cdiv(o->n_units, per));
   o->off_part = std::max(kOneCounterBytes, align_up(4 * int64_t(o->n_panels), kAlign));
   o->ws_bytes = o->off_part + 2 * int64_t(o->grid) * o->rp * batch * 4;
+  return true;
+}
+
+// The grouped format of one matrix at batch B: `rows` batch rows in one launch
+// (grid.y), each a batch-1 problem of its own with the runs, partial-row
+// slots and counters of `o` (those of row b behind those of row b - 1).  All
+// rows' workgroups are resident together (max_wg of them); fewer rows where
+// their counters don't fit in front of the partial rows.  ws_bytes holds for
+// every batch, so one workspace serves them all.
+inline bool rows_shape_for(const qtea_desc& d, int batch, int max_wg, int rp, OneShape* o, int* rows) {
+  if (!one_shape_for(d, 1, max_wg, rp, o)) return false;
+  *rows = int(std::min<int64_t>({int64_t(batch), int64_t(max_wg), o->off_part / 4 / o->n_panels}));
+  if (*rows > 1 && !one_shape_for(d, 1, max_wg / *rows, rp, o)) return false;
+  o->ws_bytes = o->off_part + 2 * std::min<int64_t>(max_wg, o->n_units * QTEA_MAX_BATCH) * o->rp * 4;
   return true;
 }
 

@@ -456,6 +456,27 @@ void check_one(const Mat& m, int batch, int max_wg, int rp) {
   CHECK(o.off_part >= 4 * int64_t(o.n_panels) && o.off_part % kAlign == 0, "one: counters overlap the parts");
 }
 
+// The grouped format's batch rows in one launch: resident together, counters
+// and partial rows of every row inside the workspace, which is one size for
+// all batches; batch 1 has one_shape_for's runs.
+void check_rows(const Mat& m, int max_wg, int rp) {
+  Layout L;
+  const qtea_desc d = make_desc(m, &L);
+  OneShape one, o;
+  CHECK(one_shape_for(d, 1, max_wg, rp, &one), "one_shape_for");
+  int64_t bytes = 0;
+  for (int batch = 1; batch <= QTEA_MAX_BATCH; ++batch) {
+    int rows = 0;
+    CHECK(rows_shape_for(d, batch, max_wg, rp, &o, &rows), "rows_shape_for");
+    CHECK(rows >= 1 && rows <= batch && o.grid * rows <= max_wg, "rows: %d x %d", rows, o.grid);
+    CHECK(batch > 1 || (rows == 1 && o.grid == one.grid), "rows: batch 1");
+    CHECK(4 * int64_t(rows) * o.n_panels <= o.off_part, "rows: counters overlap the parts");
+    CHECK(8 * int64_t(o.grid) * rows * rp <= o.ws_bytes - o.off_part, "rows: slots past the workspace");
+    CHECK(batch == 1 || o.ws_bytes == bytes, "rows: workspace differs by batch");
+    bytes = o.ws_bytes;
+  }
+}
+
 std::vector<Mat> stack(const int64_t (*shapes)[2], int n_shapes, int layers, double frac, int layout) {
   std::vector<Mat> v;
   for (int l = 0; l < layers; ++l)
@@ -577,11 +598,16 @@ int main() {
         check_one(m, 1, 512, 512);
         for (int b : {2, 4, 8, 9, 16}) check_one(m, b, 256, kOneMmaRows);
         for (int wgs : {1, 3, 7, 100}) check_one(m, 1, wgs, 512);
+        if (layout == kLayoutG128)
+          for (int wgs : {512, 1, 3, 7, 100}) check_rows(m, wgs, 512);
       }
   for (const Mat& m : edge) {
     check_one(m, 1, 512, 512);
     check_one(m, 16, 256, kOneMmaRows);
+    if (m.layout == kLayoutG128) check_rows(m, 512, 512);
   }
+  // 12500 panels: their counters leave room for one row per launch
+  check_rows(Mat{6400000, 5, 1, kLayoutG128}, 512, 512);
   printf("ok one-matrix runs (%d checks)\n", g_checks);
   return 0;
 }

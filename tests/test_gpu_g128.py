@@ -188,3 +188,29 @@ def test_g128_batch_4_synth_8b_shapes():
         got = y.cpu().numpy()[:, rows]
         assert_close(got, ref, c["x"], wmax, f"g128 B=4 {N}x{K}")
         assert_precise(got, ref, f"g128 B=4 {N}x{K}")
+
+
+@pytest.mark.parametrize("N,K,nS", [(64, 70, 0), (516, 259, 9), (2052, 1500, 31), (6144, 4096, 205)])
+def test_g128_batch_rows_share_a_launch(N, K, nS):
+    """The rows of a batch run in one launch, each with its own counters and
+    partial rows: one workspace through several batches in turn (each leaves
+    the counters zero for the next), bit for bit on dyadic inputs; the
+    allocation-free call gives the same bits."""
+    import torch
+
+    import paper_2609_00224_amd as q
+
+    c = g128_dyadic_case(400 + N, N, K, 16, nS)
+    pm = gpu_pack_g128(c)
+    ref = oracle_rows_g128(c, need_wmax=False)[0]
+    x = to_dev(c["x"])
+    ws = q.new_workspace(pm.desc, 1)
+    for B in (16, 3, 1, 5, 2, 11):
+        _report(f"one launch for the batch, {N}x{K} B={B}")
+        y = torch.full((B, N), float("nan"), dtype=torch.float32, device="cuda")
+        q.qtea_gemm_lowbatch(pm.desc, pm.packed, x[:B], B, y, ws)
+        y2 = torch.full_like(y, float("nan"))
+        q.qtea_gemm_lowbatch_noalloc(pm.desc, pm.packed, x[:B], B, y2)
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy().astype(np.float64), ref[:B]), (N, K, B)
+        assert torch.equal(y, y2)
