@@ -221,7 +221,8 @@ int qtea_gemv(const qtea_desc* desc, const void* packed, const uint16_t* x, floa
  *   X  device fp16 [batch][K] row-major;  Y  device fp32 [batch][N] row-major.
  * Batch 1..8 runs the matrix cores on the exact ternary codes in FP4, with the
  * activations v_j x_j in fixed point, 28 bits to a block of 20 columns, as six
- * digits; batch 9..16 on the codes in fp16 with the activations split into
+ * digits (a slice with blocks whose largest activation leaves several columns
+ * below 2^-6 of it: 47 bits at batch 1, 37 at 2..8); batch 9..16 on the codes in fp16 with the activations split into
  * two fp16 halves; fp32 accumulation.  (The grouped format, and matrices
  * too large for the batch-1 form's workspace, run the table-lookup kernel.)
  * An activation that is not finite makes every output of its row NaN, as

@@ -88,27 +88,72 @@ __device__ __forceinline__ int fresh(int x) {
   return x;
 }
 
-// The digits of one pack's five a_i = v_i x_i (v in the low halves of v5) and
-// of the other three packs of its quad: the five codes of digit l at
-// bits 6 i of P[l], ex the block's biased exponent (its digit l has the E8M0
-// scale ex + 5 l - 24), mx its largest |a| as bits.
-__device__ __forceinline__ void tern_digits(const uint32_t (&v5)[5], const uint16_t (&x5)[5], uint32_t (&P)[kDigits],
-                                            uint32_t& ex, uint32_t& mx) {
-  float a[5];
+// The products a_i = v_i x_i of one pack's five columns (v and x in the
+// low halves of v5 and x5): exact, 22 bits each.
+__device__ __forceinline__ void tern_products(const uint32_t (&v5)[5], const uint32_t (&x5)[5], float (&a)[5]) {
+#pragma unroll
+  for (int i = 0; i < 5; ++i)
+    a[i] = float(__builtin_bit_cast(_Float16, uint16_t(v5[i] & 0xffffu))) * float(__builtin_bit_cast(_Float16, uint16_t(x5[i])));
+}
+
+// The sum over the four lanes of a quad.
+__device__ __forceinline__ uint32_t quad_sum(uint32_t x) {
+  const uint32_t y = x + uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0xB1, 0xf, 0xf, true));    // 1,0,3,2
+  return y + uint32_t(__builtin_amdgcn_update_dpp(0, int(y), 0x4E, 0xf, 0xf, true));                // 2,3,0,1
+}
+
+// The fixed point of one pack's five a_i and of the other three packs of its
+// quad (a block of 20 columns): f[i] = a_i 2^(154 - ex) rounded to a whole
+// number, |f| <= 2^28; ex the block's biased exponent, mx its largest |a| as bits.
+__device__ __forceinline__ float tern_unit(uint32_t ex) { return __builtin_bit_cast(float, (281u - ex) << 23); }
+__device__ __forceinline__ void tern_fixed(const float (&a)[5], float (&f)[5], uint32_t& ex, uint32_t& mx) {
   mx = 0;
 #pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    a[i] = float(__builtin_bit_cast(_Float16, uint16_t(v5[i] & 0xffffu))) * float(__builtin_bit_cast(_Float16, x5[i]));
-    mx = max(mx, __builtin_bit_cast(uint32_t, a[i]) & 0x7fffffffu);
-  }
+  for (int i = 0; i < 5; ++i) mx = max(mx, __builtin_bit_cast(uint32_t, a[i]) & 0x7fffffffu);
   mx = quad_max(mx);
   ex = max(mx >> 23, 64u);  // |a| >= 2^-48 unless zero
-  const float scale = __builtin_bit_cast(float, (281u - ex) << 23);  // |a| scale < 2^28
+#pragma unroll
+  for (int i = 0; i < 5; ++i) f[i] = __builtin_rintf(a[i] * tern_unit(ex));
+}
+
+// Whether the wave's slice needs a second set of ND digits, for what the first
+// leaves of the a_i: then f becomes that, in units of 2^(1 - 5 ND) of the first's.
+// The first set rounds an a_i below 2^-6 of its block's power of two to 2^-28 of
+// it: nothing beside the block's other columns, unless many of them are that
+// small.  Then a row whose codes at the few large columns are 0 would be left
+// with the rounding (an outlier of 16000 among N(0, 1): 2.5e-6 of such a row at
+// K = 4096, with the second set 8e-8; fp32 sums: 1.1e-7).  The line is five of
+// the block's columns, in a block that has a whole pack below about 2^-3 (its
+// top digits `top` are 0: a test that costs the other slices two
+// instructions, where the count below cost 0.15 to 0.3 us per unit).  N(0, 1)
+// activations pass the line in one of 500 slices.
+template <int ND>
+__device__ __forceinline__ bool tern_rest(const float (&a)[5], float (&f)[5], uint32_t ex, uint32_t top) {
+  if (__ballot(top == 0u) == 0) return false;
+  uint32_t low = 0;
+  bool left = false;
+  float r[5];
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    r[i] = __builtin_fmaf(a[i], tern_unit(ex), -f[i]);  // (exact: fewer bits than a_i)
+    left |= r[i] != 0.0f;
+    low += __builtin_fabsf(f[i]) < 0x1p21f ? 1u : 0u;
+  }
+  low = quad_sum(low);
+  if (__ballot(left && low >= 5u) == 0) return false;  // (zeros are small and leave nothing)
+#pragma unroll
+  for (int i = 0; i < 5; ++i) f[i] = __builtin_rintf(r[i] * float(1 << (5 * ND - 1)));
+  return true;
+}
+
+// The base-32 digits of f: the five codes of digit l at bits 6 i of P[l].
+template <int ND>
+__device__ __forceinline__ void tern_digits(const float (&f)[5], uint32_t (&P)[ND]) {
   uint32_t uq[5];
 #pragma unroll
-  for (int i = 0; i < 5; ++i) uq[i] = uint32_t(int(__builtin_rintf(a[i] * scale))) + kDigitBias;
+  for (int i = 0; i < 5; ++i) uq[i] = uint32_t(int(f[i])) + (kDigitBias & ((1u << (5 * ND)) - 1u));
 #pragma unroll
-  for (int l = 0; l < kDigits; ++l) {
+  for (int l = 0; l < ND; ++l) {
     uint32_t F = 0;  // per column the digit + 16 at bits 6 i .. 6 i + 4
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
@@ -121,9 +166,14 @@ __device__ __forceinline__ void tern_digits(const uint32_t (&v5)[5], const uint1
     P[l] = ((F & (15u * kOnes)) ^ ((s << 4) - s)) + (s + (s << 5));
   }
 }
-// E8M0 scale of digit l of such a block (NaN when an activation is not finite).
+// E8M0 scale of digit l of such a block, in the first set and in a second of
+// ND (NaN when an activation is not finite).
 __device__ __forceinline__ uint8_t tern_scale(uint32_t ex, uint32_t mx, int l) {
   return uint8_t(mx >= 0x7f800000u ? 255u : ex + 5u * uint32_t(l) - 24u);
+}
+template <int ND>
+__device__ __forceinline__ uint8_t tern_rest_scale(uint32_t ex, uint32_t mx, int l) {
+  return uint8_t(mx >= 0x7f800000u ? 255u : ex + 5u * uint32_t(l) - uint32_t(23 + 5 * ND));
 }
 // The value of the quad's lane 1 or 2, in its lane 0.
 __device__ __forceinline__ uint32_t quad_next(uint32_t x) {

@@ -16,9 +16,11 @@
 //     exponent of the largest |a| of a block of 20 columns, digit l of the
 //     block has the block scale 2^(E + 5 l - 151): the instruction's E8M0
 //     scale operand (one per 32 operand columns, which is one block).  An
-//     a_j (22 bits) down to 2^-5 of its block's largest is represented
-//     exactly, the others to 2^-28 of that.  A block with an a_j that is not
-//     finite takes the NaN scale: every output of that batch row is then NaN.
+//     a_j (22 bits) down to 2^-6 of its block's power of two is represented
+//     exactly, the others to 2^-28 of that.  Where that matters (an outlier
+//     among small columns: tern_rest) two more digits hold what is left, to
+//     2^-37 of it.  A block with an a_j that is not finite takes the NaN
+//     scale: every output of that batch row is then NaN.
 //
 // Each digit has its own row of the 16 x 16 result, so the digits' sums are
 // sums of small integers (exact in fp32 as long as the blocks' scales stay
@@ -26,7 +28,9 @@
 // digit first, at the end of a panel part: y = alpha_r sum + residual.
 //
 // Result rows (of the 16 NB): batch row b = kg + 4 j owns lane group kg's
-// result registers 6 j .. 6 j + 5 (NB = 2: batch 2..4, NB = 3: 5..8).
+// result registers 6 j .. 6 j + 5 (NB = 2: batch 2..4, the two more digits in
+// its registers 6 and 7; NB = 3: 5..8, those digits as a result block of their
+// own, which only the slices that have some multiply).
 //
 // Why this form.  The kernel of grouped_mma.hip decodes a byte to fp16 codes
 // with two LDS reads (10 bytes) and about 5.6 VALU.  Here it is one 4-byte LDS
@@ -34,7 +38,8 @@
 // per result block and 1024 packed bytes) takes five times as many codes, and
 // the decode table is 31 KB instead of 93.  What it pays for is the digits:
 // about 240 VALU per batch row and slice.  Relative L2 error against 64 bits
-// 4e-8 to 7e-8 (fp16 halves: 7e-8 to 1.4e-7).  What bounds it: VALU issue (the
+// 4e-8 to 7e-8 at K = 4096 (fp16 halves: 7e-8 to 1.4e-7), with or without
+// outliers of 100 to 60000 among N(0, 1) activations.  What bounds it: VALU issue (the
 // 8B stack at batch 4 takes 385 us per call, 327 without the digits' build,
 // 344 without the residual, 262 without decode too: the weight stream).
 // A form at batch 1 (one result block, 64-row tiles on 16 waves or 256-row
@@ -71,6 +76,7 @@ namespace {
 
 // batch rows of the kernel with NB result blocks, at most
 constexpr int tern_bm(int NB) { return NB == 2 ? 4 : 8; }
+constexpr int kRest = 2;  // digits of a second set
 
 template <int NB, int WAVES, int TW>
 struct TLds {
@@ -79,7 +85,12 @@ struct TLds {
   static constexpr int IMG1 = kUnitMfma * NB * 64 * 16;     // first 16 bytes of every lane's operand
   static constexpr int IMGB = kUnitMfma * NB * 64 * 24;     // one buffer: those, then the last 8 bytes
   static constexpr int SC = IMG + 2 * IMGB;                 // u32 [2][NB][64]: E8M0 scales, byte i for instruction i
-  static constexpr int BYTES = SC + 2 * NB * 256;
+  // NB = 3: the second sets' operands and scales, [2 buffers], for the batch
+  // rows marked in RFLAG, u32 [2 buffers][8]
+  static constexpr int RIMG = SC + 2 * NB * 256;
+  static constexpr int RIMGB = kUnitMfma * 64 * 24 + 256;
+  static constexpr int RFLAG = RIMG + (NB == 3 ? 2 * RIMGB : 0);
+  static constexpr int BYTES = RFLAG + (NB == 3 ? 64 : 0);
   // In the holes: the ring of the salient activations, u16 [batch row][32
   // RING ranks], and the staging areas.  A unit's waves read ring chunks of 32
   // ranks from the one holding the unit's first salient column (less up to 31
@@ -166,8 +177,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void tern_mfma_kernel(const 
   // it less than the same digits split over both, since every task converts
   // and scales its activations.)
   static_assert(L::BM <= WAVES, "a wave per batch row");
-  uint16_t xr[5];
-  uint32_t vr[5];
+  uint32_t xr[5], vr[5];
   // (columns past the last and batch rows past the launch's read zero)
   auto load_xv = [&](const Cursor cc) {
     const GProblem& pr = PR(cc.m);
@@ -188,46 +198,105 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void tern_mfma_kernel(const 
   };
   // images of the loaded slice into buffer bb; its salient activations into
   // the ring, the first xb ranks after the first of chunk rc0
+  // NB = 2: the second sets have the batch rows' last two result rows, which
+  // hold zeros in the slices without one.  clear_rest: zeros there, in buffer bb,
+  // for this wave's batch row (lanes 0..31: instruction, column group, row).
+  auto clear_rest = [&](int bb, int lane) {
+    if (lane >= 32) return;
+    const uint32_t pi = uint32_t(lane) & 3u, m = 4u * uint32_t(w) + 2u + uint32_t(lane >> 4) + 16u * (uint32_t(lane >> 2) & 3u);
+    const uint32_t rec = (pi * NB + 1u) * 64u + (m ^ pi), img = uint32_t(L::IMG + bb * L::IMGB);
+    lds_write<u32x4>(img + rec * 16u, u32x4{0u, 0u, 0u, 0u});
+    lds_write<u32x2>(img + uint32_t(L::IMG1) + rec * 8u, u32x2{0u, 0u});
+    lds_write<uint32_t>(uint32_t(L::SC + bb * NB * 256) + (64u + m) * 4u, 0u);
+  };
+  uint32_t used = 0;  // bit bb: buffer bb holds a second set
+  if (ONE && NB == 2 && w < B) {
+    clear_rest(0, lane);
+    clear_rest(1, lane);
+  }
   auto build = [&](int bb, int rc0, int xb) {
     if (w >= B) return;  // uniform
     const int lane = fresh(tid & 63), kg = lane >> 4, b = w;
     const uint32_t pi = uint32_t(lane >> 2) & 3u, pp = uint32_t(lane) & 3u;  // instruction and dword group of the pack
     const uint32_t img = uint32_t(L::IMG + bb * L::IMGB), img2 = img + uint32_t(L::IMG1);
     const uint32_t sc = uint32_t(L::SC + bb * NB * 256);
-    uint32_t P[kDigits], ex, mx;
-    tern_digits(vr, xr, P, ex, mx);
+    float a[5], f[5];
+    uint32_t ex, mx, top = 0;
+    // (opaque, in 32 bits: the compiler packed x's values in pairs where they
+    // were loaded, behind a wait for them)
+#pragma unroll
+    for (int i = 0; i < 5; ++i) asm volatile("" : "+v"(xr[i]));
+    tern_products(vr, xr, a);
+    tern_fixed(a, f, ex, mx);
     // A quad of lanes holds the four packs of one instruction, column group
     // and digit: 30-bit codes at bits 0, 48, 96, 144 of the operand.  Its
     // first lane writes the first four dwords, its last lane the other two.
-    uint32_t P1[kDigits], P2[kDigits];
+    // Digit l goes to the operand record that row(l) names (address of its
+    // first 16 bytes, of its last 8, of its scales).
+    auto put = [&](auto nd, auto row, auto scale) {
+      constexpr int ND = decltype(nd)::value;
+      uint32_t P[ND], P1[ND], P2[ND];
+      tern_digits<ND>(f, P);
+      top = P[ND - 1];
 #pragma unroll
-    for (int l = 0; l < kDigits; ++l) {
-      P1[l] = quad_next(P[l]);
-      P2[l] = quad_next2(P[l]);
-    }
-    // operand record of result row (b, l)
-    auto record = [&](int l, uint32_t& nb, uint32_t& m) -> uint32_t {
-      const uint32_t slot = uint32_t(kDigits * (b >> 2) + l);
-      nb = slot >> 2;
-      m = 4u * uint32_t(b & 3) + (slot & 3u);
-      return (pi * NB + nb) * 64u + ((m + 16u * uint32_t(kg)) ^ pi);
+      for (int l = 0; l < ND; ++l) {
+        P1[l] = quad_next(P[l]);
+        P2[l] = quad_next2(P[l]);
+      }
+      if (pp == 0u) {
+#pragma unroll
+        for (int l = 0; l < ND; ++l) {
+          uint32_t at16, at8, at_scale;
+          row(l, at16, at8, at_scale);
+          lds_write<u32x4>(at16, u32x4{P[l], P1[l] << 16, P1[l] >> 16, P2[l]});
+          lds_write<uint8_t>(at_scale + pi, scale(l));
+        }
+      }
+      if (pp == 3u) {
+#pragma unroll
+        for (int l = 0; l < ND; ++l) {
+          uint32_t at16, at8, at_scale;
+          row(l, at16, at8, at_scale);
+          lds_write<u32x2>(at8, u32x2{P[l] << 16, P[l] >> 16});
+        }
+      }
     };
-    if (pp == 0u) {
-#pragma unroll
-      for (int l = 0; l < kDigits; ++l) {
-        uint32_t nb, m;
-        const uint32_t rec = record(l, nb, m);
-        lds_write<u32x4>(img + rec * 16u, u32x4{P[l], P1[l] << 16, P1[l] >> 16, P2[l]});
-        lds_write<uint8_t>(sc + (nb * 64u + m + 16u * uint32_t(kg)) * 4u + pi, tern_scale(ex, mx, l));
+    // slot s of batch row b: result row 4 (b mod 4) + s mod 4 of block s / 4
+    auto slot = [&](uint32_t s, uint32_t& at16, uint32_t& at8, uint32_t& at_scale) {
+      const uint32_t nb = s >> 2, m = 4u * uint32_t(b & 3) + (s & 3u) + 16u * uint32_t(kg);
+      const uint32_t rec = (pi * NB + nb) * 64u + (m ^ pi);
+      at16 = img + rec * 16u;
+      at8 = img2 + rec * 8u;
+      at_scale = sc + (nb * 64u + m) * 4u;
+    };
+    put(std::integral_constant<int, kDigits>{},
+        [&](int l, uint32_t& r, uint32_t& r2, uint32_t& rs) { slot(uint32_t(kDigits * (b >> 2) + l), r, r2, rs); },
+        [&](int l) { return tern_scale(ex, mx, l); });
+    const bool rest = tern_rest<kRest>(a, f, ex, top);
+    constexpr std::integral_constant<int, kRest> nr{};
+    if constexpr (NB == 2) {
+      if (rest) {
+        put(
+            nr, [&](int l, uint32_t& r, uint32_t& r2, uint32_t& rs) { slot(uint32_t(kDigits + l), r, r2, rs); },
+            [&](int l) { return tern_rest_scale<kRest>(ex, mx, l); });
+        used |= 1u << bb;
+      } else if ((used >> bb) & 1u) {
+        clear_rest(bb, lane);
+        used &= ~(1u << bb);
       }
-    }
-    if (pp == 3u) {
-#pragma unroll
-      for (int l = 0; l < kDigits; ++l) {
-        uint32_t nb, m;
-        const uint32_t rec = record(l, nb, m);
-        lds_write<u32x2>(img2 + rec * 8u, u32x2{P[l] << 16, P[l] >> 16});
-      }
+    } else {
+      if (rest)
+        put(
+            nr,
+            [&](int l, uint32_t& r, uint32_t& r2, uint32_t& rs) {
+              const uint32_t m = 4u * uint32_t(b & 3) + uint32_t(2 * (b >> 2) + l) + 16u * uint32_t(kg);
+              const uint32_t rec = pi * 64u + (m ^ pi), rimg = uint32_t(L::RIMG + bb * L::RIMGB);
+              r = rimg + rec * 16u;
+              r2 = rimg + uint32_t(kUnitMfma * 64 * 16) + rec * 8u;
+              rs = rimg + uint32_t(kUnitMfma * 64 * 24) + 4u * m;
+            },
+            [&](int l) { return tern_rest_scale<kRest>(ex, mx, l); });
+      lds_write<uint32_t>(uint32_t(L::RFLAG + 32 * bb + 4 * b), rest ? 1u : 0u);
     }
     // the batch row's salient activations
     const uint32_t first = uint32_t(32 * rc0 - 1 + xb);
@@ -236,7 +305,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void tern_mfma_kernel(const 
       const uint32_t rk = vr[i] >> 16;
       if (rk != 0u) {
         const uint32_t pos = first + rk, wrapped = min(pos, pos - uint32_t(32 * L::RING));
-        lds_write<uint16_t>(hole(uint32_t(b) * uint32_t(L::RING * 64) + 2u * wrapped), xr[i]);
+        lds_write<uint16_t>(hole(uint32_t(b) * uint32_t(L::RING * 64) + 2u * wrapped), uint16_t(xr[i]));
       }
     }
   };
@@ -380,7 +449,9 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void tern_mfma_kernel(const 
   __syncthreads();
 
   const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-  f32x4 C[TW][4][NB];
+  f32x4 C[TW][4][NB], R3[NB == 3 ? 4 : 1];
+#pragma unroll
+  for (f32x4& r : R3) r = zero4;
 #pragma unroll
   for (int tw = 0; tw < TW; ++tw) {
 #pragma unroll
@@ -489,6 +560,29 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void tern_mfma_kernel(const 
         // below the image build and holds every decoded dword in registers
         asm volatile("" : "+v"(C[tw][q][nb]));
       };
+      // NB = 3: the second sets' products (result rows of batch rows without
+      // one: whatever their operands hold is masked)
+      uint32_t rest = 0, flag = 0;
+      if constexpr (NB == 3) flag = lds_read<uint32_t>(uint32_t(L::RFLAG + 32 * sb) + 4u * uint32_t(lane & 7));
+      auto product_rest = [&](auto ic, const uint32_t (&e)[4][4]) {
+        constexpr int i = decltype(ic)::value;
+        if (i == 0) rest = uint32_t(__ballot(lane < B && flag != 0u));
+        if (rest == 0u) return;  // uniform
+        const int lane = fresh(tid & 63), n16 = lane & 15;
+        const uint32_t rimg = uint32_t(L::RIMG + sb * L::RIMGB), rec = uint32_t(64 * i + (lane ^ i));
+        u32x4 d = lds_read<u32x4>(rimg + 16u * rec);
+        u32x2 d2 = lds_read<u32x2>(rimg + uint32_t(kUnitMfma * 64 * 16) + 8u * rec);
+        uint32_t sc = lds_read<uint32_t>(rimg + uint32_t(kUnitMfma * 64 * 24) + 4u * uint32_t(lane));
+        const uint32_t have = 0u - ((rest >> ((n16 >> 2) + 4 * ((n16 >> 1) & 1))) & 1u);
+        d &= have;
+        d2 &= have;
+        sc &= have;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          R3[q] = tern_mfma<i>(d, d2, e[q], R3[q], sc);
+          asm volatile("" : "+v"(R3[q]));
+        }
+      };
       constexpr std::integral_constant<int, 0> i0{};
       constexpr std::integral_constant<int, 1> i1{};
       constexpr std::integral_constant<int, 2> i2{};
@@ -517,6 +611,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void tern_mfma_kernel(const 
 #pragma unroll
             for (int q = 0; q < 4; ++q) product(ic, tw, q, nb, d, d2, e[q]);
           }
+          product_rest(ic, e);
           __builtin_amdgcn_sched_barrier(0);
         };
 #pragma unroll
@@ -608,6 +703,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void tern_mfma_kernel(const 
             const f32x4(&Cq)[NB] = C[tw][q];
             float s = 0.0f;
 #pragma unroll
+            for (int d = 0; d < kRest; ++d) s += NB == 2 ? Cq[1][2 + d] : R3[q][2 * jb + d];
+#pragma unroll
             for (int d = 0; d < kDigits; ++d) s += Cq[(kDigits * jb + d) >> 2][(kDigits * jb + d) & 3];
 #ifdef QTEA_DEBUG
             if ((bad >> (4 * tw + q)) & 1u) s = __builtin_nanf("");
@@ -642,6 +739,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES / 4) void tern_mfma_kernel(const 
 #pragma unroll
           for (int nb = 0; nb < NB; ++nb) C[tw][q][nb] = zero4;
       }
+#pragma unroll
+      for (f32x4& r : R3) r = zero4;
 #ifdef QTEA_DEBUG
       bad = 0;
 #endif

@@ -28,8 +28,12 @@
 // 4096 7.1 (7.7), 6144 x 4096 7.2 (8.3), 28672 x 4096 11.0 (13.2), 4096 x 14336
 // 9.5 (12.5, four parts here), 3076 x 2999 5.9 (7.1), 512 x 700 3.7 (6.3); the 8B
 // stack's 128 products called one by one 1123 (1409) us.  Whole 64-row tiles
-// at 4096 x 4096: 7.6.  Relative L2 error against 64 bits 8e-8 to 9e-8 (table
-// sums: 1.1e-7 to 1.2e-7).
+// at 4096 x 4096: 7.6.  Relative L2 error against 64 bits 8e-8 to 1.1e-7 (table
+// sums: 1e-7 to 1.3e-7), with or without outliers of 100 to 60000 among N(0, 1)
+// activations: a slice that has some takes four more digits (tern_rest), in
+// result rows that are there anyway; looking for them costs 0.1 us.
+#include <type_traits>
+
 #include "tern_common.h"
 
 namespace qtea_grouped {
@@ -41,6 +45,7 @@ constexpr int kSoloImg = kUnitMfma * 32 * 24;         // (result rows 0..7, 4 co
 constexpr int kSoloArea = kSoloImg + 128;             // and their scales, u32 per record
 static_assert(kSoloArea >= kStage, "a residual wave stages its values in the same area");
 constexpr int kSoloRed = kTab + kSoloWaves * kSoloArea;          // fp32 [2][task][64] row sums
+constexpr int kSoloRest = 4;                          // digits of a second set
 constexpr int kSoloBytes = kSoloRed + 2 * kSoloWaves * 64 * 4;
 
 // QN: 16-row tiles (of a 64-row tile's four) that the workgroups walk over
@@ -110,8 +115,7 @@ __global__ __launch_bounds__(kSoloWaves * 64, 4) void tern_solo_kernel(const GPr
       W[q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, int(w_lo),
                                                                               int(uint32_t(t / SPLIT) * tile_bytes) + q_row(t % SPLIT * QN + q) * kGroupPacks, kAuxNT));
     };
-    uint32_t vr[5];
-    uint16_t xr[5];
+    uint32_t xr[5], vr[5];
 #pragma unroll
     for (int q = 0; q < QN; ++q) load_w(q, t0);
     // columns past the last read zero
@@ -132,41 +136,57 @@ __global__ __launch_bounds__(kSoloWaves * 64, 4) void tern_solo_kernel(const GPr
     // the digits' operands, which stay for the launch
     u32x4 D[4];
     u32x2 D2[4];
-    uint32_t P[kDigits], ex, mx;
-    tern_digits(vr, xr, P, ex, mx);
-    const uint32_t pi = uint32_t(lane >> 2) & 3u, pp = uint32_t(lane) & 3u;  // instruction and dword group of the pack
-    uint32_t P1[kDigits], P2[kDigits];
-#pragma unroll
-    for (int l = 0; l < kDigits; ++l) {
-      P1[l] = quad_next(P[l]);
-      P2[l] = quad_next2(P[l]);
-    }
-    // digit l is result row l; record (row, column group) of instruction i at (row + 8 group) ^ i
-    if (pp == 0u) {
-#pragma unroll
-      for (int l = 0; l < kDigits; ++l) {
-        const uint32_t rec = pi * 32u + ((uint32_t(l) + 8u * uint32_t(kg)) ^ pi);
-        lds_write<u32x4>(area + rec * 16u, u32x4{P[l], P1[l] << 16, P1[l] >> 16, P2[l]});
-        lds_write<uint8_t>(area + uint32_t(kSoloImg) + (uint32_t(l) + 8u * uint32_t(kg)) * 4u + pi, tern_scale(ex, mx, l));
-      }
-    }
-    if (pp == 3u) {
-#pragma unroll
-      for (int l = 0; l < kDigits; ++l) {
-        const uint32_t rec = pi * 32u + ((uint32_t(l) + 8u * uint32_t(kg)) ^ pi);
-        lds_write<u32x2>(area + uint32_t(kSoloImg1) + rec * 8u, u32x2{P[l] << 16, P[l] >> 16});
-      }
-    }
-    asm volatile("" ::: "memory");  // (this wave's own area: in order)
-    // (result rows 8..15 repeat 0..7, rows 6 and 7 hold no digit: not read)
+    uint32_t scv;
+    float a[5], f[5];
+    uint32_t ex, mx, top = 0;
+    // (result rows 6 and 7 hold no digit: not read)
     const uint32_t r0 = uint32_t(n16 & 7) + 8u * uint32_t(kg);
+    // the digits of f as the operands of the lanes that take them, through the wave's area
+    auto operands = [&](auto nd, bool take, auto scale) {
+      constexpr int ND = decltype(nd)::value;
+      uint32_t P[ND], P1[ND], P2[ND];
+      tern_digits<ND>(f, P);
+      top = P[ND - 1];
+      const uint32_t pi = uint32_t(lane >> 2) & 3u, pp = uint32_t(lane) & 3u;  // instruction and dword group of the pack
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t rec = uint32_t(i) * 32u + (r0 ^ uint32_t(i));
-      D[i] = lds_read<u32x4>(area + rec * 16u);
-      D2[i] = lds_read<u32x2>(area + uint32_t(kSoloImg1) + rec * 8u);
-    }
-    const uint32_t scv = lds_read<uint32_t>(area + uint32_t(kSoloImg) + r0 * 4u);
+      for (int l = 0; l < ND; ++l) {
+        P1[l] = quad_next(P[l]);
+        P2[l] = quad_next2(P[l]);
+      }
+      // digit l is result row l; record (row, column group) of instruction i at (row + 8 group) ^ i
+      if (pp == 0u) {
+#pragma unroll
+        for (int l = 0; l < ND; ++l) {
+          const uint32_t rec = pi * 32u + ((uint32_t(l) + 8u * uint32_t(kg)) ^ pi);
+          lds_write<u32x4>(area + rec * 16u, u32x4{P[l], P1[l] << 16, P1[l] >> 16, P2[l]});
+          lds_write<uint8_t>(area + uint32_t(kSoloImg) + (uint32_t(l) + 8u * uint32_t(kg)) * 4u + pi, scale(l));
+        }
+      }
+      if (pp == 3u) {
+#pragma unroll
+        for (int l = 0; l < ND; ++l) {
+          const uint32_t rec = pi * 32u + ((uint32_t(l) + 8u * uint32_t(kg)) ^ pi);
+          lds_write<u32x2>(area + uint32_t(kSoloImg1) + rec * 8u, u32x2{P[l] << 16, P[l] >> 16});
+        }
+      }
+      asm volatile("" ::: "memory");  // (this wave's own area: in order)
+      if (take) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t rec = uint32_t(i) * 32u + (r0 ^ uint32_t(i));
+          D[i] = lds_read<u32x4>(area + rec * 16u);
+          D2[i] = lds_read<u32x2>(area + uint32_t(kSoloImg1) + rec * 8u);
+        }
+        scv = lds_read<uint32_t>(area + uint32_t(kSoloImg) + r0 * 4u);
+      }
+      asm volatile("" ::: "memory");
+    };
+    tern_products(vr, xr, a);
+    tern_fixed(a, f, ex, mx);
+    operands(std::integral_constant<int, kDigits>{}, true, [&](int l) { return tern_scale(ex, mx, l); });  // result rows 8..15 repeat 0..7 ...
+    const bool rest = tern_rest<kSoloRest>(a, f, ex, top);
+    if (rest)
+      operands(std::integral_constant<int, kSoloRest>{}, n16 >= 8, [&](int l) { return tern_rest_scale<kSoloRest>(ex, mx, l); });  // ... or are the second set's
     __syncthreads();  // the decode table is complete
     walk([&](int t, int tn, uint32_t out) {
       (void)t;
@@ -222,11 +242,12 @@ __global__ __launch_bounds__(kSoloWaves * 64, 4) void tern_solo_kernel(const GPr
 #endif
 #pragma unroll
       for (int q = 0; q < QN; ++q) {
-        // lane group 0 holds digits 0..3, group 1 digits 4 and 5
+        // lane group 0 holds digits 0..3, group 1 digits 4 and 5, group 2 the second set's
         const float s4 = C[q][0] + C[q][1];
         const float s6 = (s4 + C[q][2]) + C[q][3];
         const float mine = (kg & 1) ? s4 : s6;
         float s = mine + __shfl_xor(mine, 16);
+        if (rest) s += __shfl(s6, lane | 32);  // (uniform; lane group 0's is stored)
 #ifdef QTEA_DEBUG
         if ((bad >> q) & 1u) s = __builtin_nanf("");
 #endif
