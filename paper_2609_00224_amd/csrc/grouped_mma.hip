@@ -11,11 +11,11 @@
 //     -1 / 0 / +1 (exact), decoded from the packed bytes by one table lookup
 //     per byte in LDS;
 //   B (32 columns x 16): a_j = v_j x[b][j] (exact in fp32: 11-bit by 11-bit
-//     significands) split into two fp16 halves hi = fp16(a), lo = fp16(a -
-//     hi), so hi + lo reproduces a (to 2^-25 absolute for |a| < 1/8, exactly
-//     above); with B <= 8 the 16 columns hold hi of every batch row and lo of
+//     significands) split into two fp16 halves hi = fp16(a), lo = fp16(2^11
+//     (a - hi)), so hi + 2^-11 lo reproduces a (to 2^-36 absolute for
+//     |a| < 2^-14, exactly above); with B <= 8 the 16 columns hold hi of every batch row and lo of
 //     every batch row, with B <= 16 hi and lo are two MFMAs (NB = 2);
-//   y[b][r] = alpha_r (C[r][hi b] + C[r][lo b]) + residual.
+//   y[b][r] = alpha_r (C[r][hi b] + 2^-11 C[r][lo b]) + residual.
 //
 // A slice whose |a| reaches the fp16 range is scaled by 2^-16 before the
 // split (and its products by 2^16 after): rare, handled on a slow path.
@@ -175,11 +175,14 @@ __device__ __forceinline__ u32x2 e4m3x4_to_half(uint32_t w) {
   return u32x2{__builtin_bit_cast(uint32_t, a) | sa, __builtin_bit_cast(uint32_t, b) | sb};
 }
 
-// fp16 hi / lo split of a (RNE both); hi + lo == a whenever a - hi is
-// representable (|a| >= 1/8), else within 2^-25.
+// fp16 hi / lo split of a (RNE both), lo in units of 2^-11: hi + 2^-11 lo == a
+// down to |a| = 2^-14, below that within 2^-36.  (In units of 1, exact down to
+// 1/8 only: activations of 0.01 lost all but 2^-25, 1.7e-6 of the result where
+// this has 7e-8.)
+constexpr float kLoScale = 1.0f / 2048.0f;
 __device__ __forceinline__ void split_hl(float a, _Float16& hi, _Float16& lo) {
   hi = (_Float16)a;
-  lo = (_Float16)(a - (float)hi);
+  lo = (_Float16)((a - (float)hi) * (1.0f / kLoScale));
 }
 
 // F8: residual values are E4M3 bytes (layout 3), else fp16 (layout 2).
@@ -520,7 +523,7 @@ __global__ __launch_bounds__((MShape<NB, ONE>::MT)) void grouped_mma_kernel(cons
             const uint32_t wd = aw[2 * q + (v >> 1)];
             const float al = float(__builtin_bit_cast(_Float16, uint16_t((v & 1) ? wd >> 16 : wd & 0xffffu)));
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) C[q][nb][v] *= al;
+            for (int nb = 0; nb < NB; ++nb) C[q][nb][v] *= nb == 1 || (NB == 1 && jr >= 8) ? al * kLoScale : al;
           }
       }
       // 2. residual of the part's salient columns: one MFMA per 32 of them.
