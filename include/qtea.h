@@ -219,12 +219,14 @@ int qtea_gemv(const qtea_desc* desc, const void* packed, const uint16_t* x, floa
  * Y = X W^T for 1 <= batch <= QTEA_MAX_BATCH activation rows (low-batch
  * decode: one token per row).
  *   X  device fp16 [batch][K] row-major;  Y  device fp32 [batch][N] row-major.
- * Batch 1..8 runs the matrix cores on the exact ternary codes in FP4, with the
+ * Batch 1..4, and 5..8 of matrices of up to two 512-row by 320-column units per
+ * compute unit, runs the matrix cores on the exact ternary codes in FP4, with the
  * activations v_j x_j in fixed point, 28 bits to a block of 20 columns, as six
  * digits (a slice with blocks whose largest activation leaves several columns
- * below 2^-6 of it: 47 bits at batch 1, 37 at 2..8); batch 9..16 on the codes in fp16 with the activations split into
- * two fp16 halves; fp32 accumulation.  (The grouped format, and matrices
- * too large for the batch-1 form's workspace, run the table-lookup kernel.)
+ * below 2^-6 of it: 47 bits at batch 1, 37 at 2..8); larger matrices at 5..8 and
+ * batch 9..16 on the codes in fp16 with the activations split into two fp16
+ * halves; fp32 accumulation.  (The grouped format, and matrices too large for
+ * the batch-1 form's workspace, run the table-lookup kernel.)
  * An activation that is not finite makes every output of its row NaN, as
  * 0 * inf does in the dense product.  Errors as qtea_gemv plus
  * QTEA_ERR_BATCH.

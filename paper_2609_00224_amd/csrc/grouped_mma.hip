@@ -1,7 +1,8 @@
-// Grouped low-batch GEMM on the matrix cores: Y_m = X_m W_m^T for 5 <= B <=
-// 16 activation rows per problem (and 9 <= B <= 16 rows of one problem on its
-// own; smaller batches run the kernel of tern_mfma.hip) (Eq. 10 with one group and zero bias, plus
-// the Eq. 11 residual), every problem of a plan in one persistent launch.
+// Grouped low-batch GEMM on the matrix cores (Eq. 10 with one group and zero
+// bias, plus the Eq. 11 residual): Y_m = X_m W_m^T for 5 <= B <= 16 activation
+// rows per problem, every problem of a plan in one persistent launch, or for
+// one problem on its own (9 <= B <= 16, and 5 <= B <= 8 of a large one:
+// launch_one_mma; smaller batches run the kernel of tern_mfma.hip).
 //
 // At batch B the product is a dense contraction of the ternary weights with
 // a B-column activation block, so it runs on v_mfma_f32_16x16x32_f16 with
@@ -61,9 +62,9 @@ namespace {
 // register budget (168 instead of 128 per lane) takes its spills from about
 // 40 registers to 5 (8B stack, batch 16: 827 -> 720 us per token; at NB = 1
 // the 768-thread shape, with no spills to remove, lost 25 % to the fewer
-// waves).  One matrix on its own (NB = 2): 512 threads (256 registers, no
-// spills, and more panels of a short launch to spread over the CUs: the 8B
-// stack chained at batch 16 takes 2685 us against 3314 with the grouped
+// waves).  One matrix on its own: 512 threads at both (256 registers, no
+// spills, and twice the panels of a short launch to spread over the CUs: the
+// 8B stack chained at batch 16 takes 2685 us against 3314 with the grouped
 // shape; 256 threads were slower again).
 template <int NB, bool ONE>
 struct MShape {
@@ -730,13 +731,20 @@ hipError_t launch_grouped_mma(const uint8_t* plan, int grid, int batch, bool f8,
 }
 
 hipError_t launch_one_mma(const GOne& one, int grid, bool f8, float* part, hipStream_t st) {
-  // Batch 2..8: the FP4 kernel, whose decode table is a third of this one's
-  // and whose decode is one LDS read per byte (4096 x 4096, batch 2 / 4 / 8:
-  // 9.4 / 9.5 / 11.0 us against 11.5 / 11.9 / 12.0; 28672 x 4096: 16.2 / 16.9 /
-  // 21.5 against 19.7 / 19.9 / 21.7, the reduce kernel included).  Above, six
-  // result blocks would not fit its registers.
+  // Batch 2..4: the FP4 kernel, whose decode table is a third of this one's and
+  // whose decode is one LDS read per byte (4096 x 4096, batch 2 / 4: 9.7 / 10.1 us
+  // against 11.9 / 12.2, 57344 x 8192: 43.0 / 43.8 against 46.4 / 46.9, the
+  // reduce kernel included).  At 5..8 its third result block and digit images
+  // cost more per unit than this kernel's, and only its start is shorter: it is
+  // the faster one up to two units per workgroup (4096 x 4096, batch 5 / 8: 11.2 /
+  // 11.6 against 12.0 / 12.4; 8192 x 8192: 15.4 / 16.2 against 15.6 / 16.2), the
+  // slower one from three (28672 x 4096: 21.5 / 22.9 against 21.0 / 22.2; 57344 x
+  // 8192: 57.4 / 60.7 against 47.2 / 49.2).  Above 8, six result blocks would not
+  // fit its registers.
+  const bool tern = one.batch <= kGroupedTernBatch || (one.batch <= kOneTernBatch && one.n_units <= 2 * grid);
   hipError_t e;
-  if (one.batch <= kOneTernBatch) e = launch_one_tern(one, grid, f8, part, st);
+  if (tern) e = launch_one_tern(one, grid, f8, part, st);
+  else if (one.batch <= 8) e = f8 ? launch<1, true, true>(nullptr, grid, part, one, st) : launch<1, false, true>(nullptr, grid, part, one, st);
   else e = f8 ? launch<2, true, true>(nullptr, grid, part, one, st) : launch<2, false, true>(nullptr, grid, part, one, st);
   if (e != hipSuccess) return e;
   bool split = false;
@@ -745,6 +753,7 @@ hipError_t launch_one_mma(const GOne& one, int grid, bool f8, float* part, hipSt
     split = one_owner(p * ns, one.n_units, grid) != one_owner(p * ns + ns - 1, one.n_units, grid);
   if (!split) return hipSuccess;
   constexpr int RP = MShape<2, true>::MRP;
+  static_assert(MShape<1, true>::MRP == RP, "one panel height for one-matrix launches");
   hipLaunchKernelGGL(one_reduce_kernel<RP>, dim3(one.pr.n_panels, one.batch), dim3(RP / 4 * kRedGroups), 0, st, one,
                      part, grid);
   return hipGetLastError();
