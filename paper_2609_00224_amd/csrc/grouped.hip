@@ -42,6 +42,7 @@
 #include <vector>
 
 #include "grouped_plan.h"
+#include "per_device.h"
 
 namespace {
 
@@ -856,23 +857,15 @@ hipError_t set_lds_attr() {
 
 // A device's workgroup counts do not change: each is asked for once per device
 // (the occupancy query alone took longer than the rest of a call's host work).
-constexpr int kMaxDevices = 64;
 template <class Query>
-int per_device(std::atomic<int> (&known)[kMaxDevices], Query query) {
+int per_current_device(std::atomic<int> (&known)[kMaxDevices], Query query) {
   int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 0;
-  if (dev >= kMaxDevices) return query(dev);
-  int n = known[dev].load(std::memory_order_relaxed);
-  if (n == 0) {
-    n = query(dev);  // (0 on failure: asked for again next time)
-    known[dev].store(n, std::memory_order_relaxed);
-  }
-  return n;
+  return hipGetDevice(&dev) == hipSuccess ? per_device(known, dev, query) : 0;
 }
 
 int cu_count() {
   static std::atomic<int> known[kMaxDevices];
-  return per_device(known, [](int dev) {
+  return per_current_device(known, [](int dev) {
     int n = 0;
     return hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 0;
   });
@@ -883,7 +876,7 @@ int cu_count() {
 // The kernel never waits for another workgroup, so any grid is correct.
 int grid_size() {
   static std::atomic<int> known[kMaxDevices];
-  return per_device(known, [](int) {
+  return per_current_device(known, [](int) {
     const int n = cu_count();
     int per = 0;
     if (n < 1 || set_lds_attr<kMaxRB, false>() != hipSuccess) return 0;

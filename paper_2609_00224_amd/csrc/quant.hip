@@ -28,6 +28,9 @@
 // kernel's own anyway.
 #include <math.h>
 
+#include <atomic>
+
+#include "per_device.h"
 #include "qtea_internal.h"
 #include "qtea_quant.h"
 
@@ -41,9 +44,9 @@ constexpr int kNBH = 32;               // panel columns staged per LDS pass of t
 static_assert(kNB <= 64, "the diagonal block's elimination maps one column per lane of a wave");
 constexpr int kCT = 64;                // threads of the row-parallel kernels (one wave)
 constexpr int kColChunk = 16;          // later columns of a block updated per workgroup
-// Most workgroups of col_block_kernel, which wait for one another: a quarter
-// of the 512 (two per CU) that the device holds, so that quantizations on
-// four streams (the hardware queues of a process) are resident together.
+// Most workgroups of col_block_kernel, which wait for one another, on any
+// device (exchange slots in the workspace): a quarter of the 512 (two per CU)
+// that 256 CUs hold.  A smaller device takes fewer (block_workgroups).
 constexpr int kXchWgs = 128;
 constexpr int64_t kQAlign = 256;
 constexpr int64_t kQMaxRows = 65536;
@@ -782,7 +785,8 @@ __global__ __launch_bounds__(kCT) void col_kernel(ColArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// One block's columns in one launch, for matrices of at most 64 kXchWgs rows.
+// One block's columns in one launch, for matrices of at most 64 rows per
+// workgroup of block_workgroups (8192 rows on 256 CUs).
 //
 // What bounds the column-by-column launches above is the launches: two
 // dependent ones per column (11.3 us), each a few hundred cycles of work on N
@@ -802,11 +806,12 @@ __global__ __launch_bounds__(kCT) void col_kernel(ColArgs a) {
 // 1.  A workgroup reaches exchange s + 2, which overwrites the slots of s,
 // only after every workgroup published s + 1, that is after all read s.
 //
-// Every wait ends: the workgroups are few enough to be resident together,
-// and a wait that lasts 20 s all the same (more such kernels at once than the
-// device holds) raises status[1], after which this and the following
-// launches return at once and the call quantizes the columns again by the
-// launches per column.
+// Every wait ends: the workgroups are few enough to be resident together
+// (block_workgroups), and a wait that lasts 0.2 s all the same (more such
+// kernels at once than the device holds, other work on all of it) raises
+// status[1], after which this and the following launches return at once and
+// the call quantizes the columns again by the launches per column.  (An
+// exchange takes 2 us; 0.2 s is a few times what a layer's column phase takes.)
 // ---------------------------------------------------------------------------
 constexpr int kCBWaves = kQG / kColChunk;  // 8
 #ifdef QTEA_DEBUG
@@ -814,7 +819,7 @@ constexpr int kCBWaves = kQG / kColChunk;  // 8
 // of more than one workgroup through the launches per column
 constexpr uint64_t kXchTicks = 0;
 #else
-constexpr uint64_t kXchTicks = 2000000000ull;  // 20 s of the 100 MHz counter
+constexpr uint64_t kXchTicks = 20000000ull;  // 0.2 s of the 100 MHz counter
 #endif
 
 struct ColBlockArgs {
@@ -1070,6 +1075,23 @@ __global__ __launch_bounds__(256) void trail_gemm_kernel(double* __restrict__ Wt
       }
 }
 
+// Most workgroups of col_block_kernel on the current device, or partition of
+// one (256 CUs: 128; 32 CUs, which hold 64: 16).
+int block_workgroups() {
+  static std::atomic<int> known[qtea_detail::kMaxDevices];
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) return 1;
+  const int resident = qtea_detail::per_device(known, dev, [](int d) {
+    int cus = 0, per = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, d) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(&col_block_kernel),
+                                                     kCBWaves * 64, 0) != hipSuccess)
+      return 0;
+    return cus * per;
+  });
+  return qtea_detail::waiting_workgroups(resident, kXchWgs);
+}
+
 int grid1(int64_t n, int per) { return int(q_cdiv(n, per) < 65535 * 16 ? q_cdiv(n, per) : 65535 * 16); }
 
 }  // namespace
@@ -1234,7 +1256,7 @@ int qtea_quantize(const double* W, const double* H, int64_t N, int64_t K, const 
     return hipGetLastError() == hipSuccess && hipStreamSynchronize(st) == hipSuccess &&
            hipMemcpy(host_status, status, sizeof(host_status), hipMemcpyDeviceToHost) == hipSuccess;
   };
-  columns(nwg <= kXchWgs);
+  columns(nwg <= block_workgroups());
   if (!finish()) return QTEA_ERR_HIP;
   if (host_status[0]) return QTEA_ERR_NOT_POSITIVE;
   if (host_status[1]) {  // the workgroups were not resident together: the launches per column need no exchange

@@ -27,7 +27,9 @@
 //     chunks did not each run once raises a flag;
 //   * one matrix on its own: the workgroup runs partition the units, none
 //     empty, one_owner inverts one_first, and the split panels' parts have
-//     distinct slots inside the workspace.
+//     distinct slots inside the workspace;
+//   * values asked for once per device: a failure is asked for again, devices
+//     do not share; and the workgroups that may wait for one another.
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -39,6 +41,7 @@
 #include <utility>
 #include <vector>
 
+#include "per_device.h"
 #include "plan_host.h"
 
 using namespace qtea_grouped;
@@ -477,6 +480,21 @@ void check_rows(const Mat& m, int max_wg, int rp) {
   }
 }
 
+void check_per_device() {
+  static std::atomic<int> known[kMaxDevices];
+  int asked = 0, answer = 0;
+  auto ask = [&](int dev) { return per_device(known, dev, [&](int d) { ++asked; return answer ? answer + d : 0; }); };
+  CHECK(ask(-1) == 0 && asked == 0, "no device");
+  CHECK(ask(0) == 0 && ask(0) == 0 && asked == 2, "a failure is asked for again");
+  answer = 7;
+  CHECK(ask(0) == 7 && ask(0) == 7 && asked == 3, "device 0 asked for once");
+  CHECK(ask(1) == 8 && ask(1) == 8 && ask(0) == 7 && asked == 4, "device 1 on its own");
+  CHECK(ask(kMaxDevices) == kMaxDevices + 7 && ask(kMaxDevices) == kMaxDevices + 7 && asked == 6, "past the table");
+  // a whole device of 256 CUs, partitions of 128, 64 and 32, one workgroup per CU, failure
+  const int holds[][2] = {{512, 128}, {256, 64}, {128, 32}, {64, 16}, {32, 8}, {3, 1}, {0, 1}, {4096, 128}};
+  for (const auto& h : holds) CHECK(waiting_workgroups(h[0], 128) == h[1], "of %d workgroups", h[0]);
+}
+
 std::vector<Mat> stack(const int64_t (*shapes)[2], int n_shapes, int layers, double frac, int layout) {
   std::vector<Mat> v;
   for (int l = 0; l < layers; ++l)
@@ -609,5 +627,8 @@ int main() {
   // 12500 panels: their counters leave room for one row per launch
   check_rows(Mat{6400000, 5, 1, kLayoutG128}, 512, 512);
   printf("ok one-matrix runs (%d checks)\n", g_checks);
+
+  check_per_device();
+  printf("ok values per device (%d checks)\n", g_checks);
   return 0;
 }

@@ -41,8 +41,8 @@ def test_column_phase_matches_oracle(N, K, nS, iters):
 @pytest.mark.parametrize("N,K,nS,iters", [(8192, 140, 3, 2), (132, 300, 4, 3)])
 def test_columns_again_when_an_exchange_runs_out(N, K, nS, iters):
     """The debug build's waits between workgroups run out at once: its call
-    quantizes the columns again by the launches per column and gives the
-    release build's bits."""
+    marks that in the workspace, quantizes the columns again by the launches
+    per column and gives the release build's bits."""
     import torch
 
     import paper_2609_00224_amd as q
@@ -51,12 +51,26 @@ def test_columns_again_when_an_exchange_runs_out(N, K, nS, iters):
     W, X = synth.quant_inputs(300 + K, N, K, 3 * K)
     W, H = torch.from_numpy(W).to("cuda"), torch.from_numpy(qz.hessian(X)).to("cuda")
     want = q.quantize_matrix(W, H, nS, iters=iters)
+    # the word after the factorization's status, 12 bytes behind the regions of
+    # W, H_d, U, a block's errors, scores, flags, ranks and block means
+    up = lambda n: -(-n // 256) * 256
+    mark = sum(map(up, (8 * K * N, 8 * K * K, 8 * K * K, 8 * 128 * N, 8 * K, 4 * K, 4 * K, 8 * -(-K // 128)))) + 12
+
+    def call():
+        out = {k: None if v is None else torch.zeros_like(v) for k, v in want.items()}
+        ws = torch.zeros(q.qtea_quant_workspace_bytes(N, K), dtype=torch.uint8, device="cuda")
+        p = q.QteaQuantParams(nS, 1.0, 0.01, iters, 0)
+        q.qtea_quantize(W, H, p, *(out[k] for k in ("T", "alpha", "beta", "v", "S", "bitmap", "R8", "idx")), None, ws)
+        return out, int(ws[mark:mark + 4].view(torch.int32).item())
+
+    assert call()[1] == 0
     saved = q._lib
     q._lib = q.open_library(q.DEBUG_LIB_PATH)
     try:
-        got = q.quantize_matrix(W, H, nS, iters=iters)
+        got, ran_out = call()
     finally:
         q._lib = saved
+    assert ran_out == 1
     for k, v in want.items():
         assert v is None or torch.equal(v, got[k]), k
 
