@@ -182,9 +182,9 @@ int qtea_pack_g128(const int8_t* trits, int64_t N, int64_t K, const uint16_t* gr
  * matrix's output rows and its K range over the workgroups of one launch;
  * rows whose shares fall to more than one workgroup are summed from their
  * partial rows in a fixed order, at batch 1 by the last of them to arrive,
- * at batch 2..16 by a second small kernel on the same stream.  The workspace holds the arrival counters (64 KB,
- * more for a matrix of more than 16384 panels; the same place for every
- * matrix) and two slots of partial rows per workgroup.  It must be zero-filled before its first use
+ * at batch 2..16 by a second small kernel on the same stream.  The workspace
+ * holds the arrival counters (64 KB, the same place for every matrix) and two
+ * slots of partial rows per workgroup.  It must be zero-filled before its first use
  * (qtea_workspace_init or any zero fill); every call that runs to
  * completion leaves the counters at zero again, so one workspace serves any
  * sequence of stream-ordered calls.  Calls that may overlap in time must
@@ -247,8 +247,7 @@ int qtea_gemm_lowbatch(const qtea_desc* desc, const void* packed, const uint16_t
  * (other streams, other host threads) race and must not be made.
  * Errors as qtea_gemm_lowbatch, with QTEA_ERR_WORKSPACE for a call whose
  * workspace (qtea_workspace_bytes) would not fit the array: on a device of
- * up to 256 CUs every batch fits a matrix of up to 16384 x 512 rows (one
- * arrival counter per 512-row panel).
+ * up to 256 CUs every batch fits a matrix of up to 16384 x 512 rows.
  */
 #define QTEA_NOALLOC_SCRATCH_BYTES (16 * 1048576 + 65536)
 int qtea_gemm_lowbatch_noalloc(const qtea_desc* desc, const void* packed, const uint16_t* X, int batch,

@@ -156,7 +156,8 @@ __device__ __forceinline__ constexpr uint32_t perm_sel(int k) {
 // ONE: a single problem launched on its own (GOne): no plan and no queue;
 // workgroup g takes the contiguous run of units [g U / G, (g + 1) U / G), and
 // a panel split between runs is summed by the last of its workgroups to
-// arrive (counters[panel] in the workspace, partial rows in `part`).
+// arrive (counted in the workspace at the index of the panel's first run: a
+// run opens at most one panel that it leaves unfinished; partial rows in `part`).
 template <int RB, bool F8, bool G128 = false, bool ONE = false, bool ROWS = false>
 __global__ __launch_bounds__(kGT) void grouped_gemv_kernel(const uint8_t* __restrict__ plan,
                                                            float* __restrict__ part,
@@ -199,7 +200,7 @@ __global__ __launch_bounds__(kGT) void grouped_gemv_kernel(const uint8_t* __rest
   const int64_t brow = ROWS ? blockIdx.y : 0;
   if constexpr (ROWS) {
     part += brow * 2 * int64_t(gridDim.x) * RP;
-    counters += brow * one.pr.n_panels;
+    counters += brow * int64_t(gridDim.x);
   }
   const int G = ONE ? int(gridDim.x) : H->n_wg, NC = ONE ? int(gridDim.x) : H->n_chunks;
   // Chunks g and g + G are this workgroup's first two; every later chunk is
@@ -756,10 +757,9 @@ __global__ __launch_bounds__(kGT) void grouped_gemv_kernel(const uint8_t* __rest
         __builtin_amdgcn_s_waitcnt(0);  // the part is complete before its arrival is counted
         __syncthreads();
         if (tid == 0) {
-          const uint32_t before = __hip_atomic_fetch_add(counters + cur.panel, 1u, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT);
+          const uint32_t before = __hip_atomic_fetch_add(counters + ga, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           const bool last = before == uint32_t(gb - ga);
-          if (last) __hip_atomic_store(counters + cur.panel, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (last) __hip_atomic_store(counters + ga, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           flag[2] = last;
         }
         __syncthreads();
@@ -924,8 +924,8 @@ hipError_t launch_one_b1(const GOne& one, int grid, int rows, float* part, uint3
   return hipGetLastError();
 }
 
-// One matrix on its own (arguments checked by the caller): the panels'
-// arrival counters at `counters` (zero on entry, left at zero), the partial
+// One matrix on its own (arguments checked by the caller): the arrival
+// counters at `counters` (zero on entry, left at zero), the partial
 // rows of split panels at `part` (2 grid slots of rp x batch floats).  The
 // grouped format runs `rows` batch rows per launch: a launch per row spent
 // most of its 9 to 14 us on its start, the first table of every workgroup and
@@ -969,7 +969,7 @@ int one_launch(const qtea_desc& d, const void* packed, const uint16_t* X, int ba
 // array's name to a kernel (on the host it is only a stand-in for the
 // symbol): the device address comes from hipGetSymbolAddress, once per
 // device with that device current, and is kept per device.  Layout: the
-// panels' arrival counters in the first kNoallocCounterBytes (zero-filled
+// arrival counters in the first kNoallocCounterBytes (zero-filled
 // once, at the first call on the device, and left at zero by every call that
 // completes), then the partial rows.
 constexpr int64_t kNoallocCounterBytes = 65536;

@@ -60,7 +60,7 @@ static_assert(sizeof(GProblem) == 128, "plan record size");
 // is a kernel argument, and workgroup g of G takes the contiguous run of
 // units [g U / G, (g + 1) U / G) of the U = n_panels * n_slices units.  A
 // panel whose units fall in more than one run is summed in run order: at
-// batch 1 by the last of its workgroups to arrive (a counter per panel in
+// batch 1 by the last of its workgroups to arrive (a counter per run in
 // the workspace), at batch 2..16 by a small reduce kernel after the launch.
 struct GOne {
   GProblem pr;
@@ -176,11 +176,13 @@ inline bool offsets_fit(const qtea_desc& d) {
 // Launch shape of one matrix on its own (qtea_gemv, qtea_gemm_lowbatch) over
 // at most max_wg workgroups of rp-row panels.  Every workgroup takes the
 // same number of units (the least that fits the grid), so no workgroup
-// carries more than the others.  The workspace holds one arrival counter
-// per panel (used at batch 1), then two partial-row slots per workgroup.
-// The counters have the same place for every matrix (up to kOneCounterBytes of
-// them): a workspace serves a sequence of matrices, and one matrix's
-// counters must not lie in another's part of the partial rows.
+// carries more than the others.  The workspace holds the arrival counters
+// (used at batch 1), then two partial-row slots per workgroup.  The counters
+// have the same place for every matrix, kOneCounterBytes in front of the
+// partial rows: a workspace serves a sequence of matrices, and one matrix's
+// counters must not lie in another's partial rows.  A split panel's counter is that
+// of the run that opens it, so that they are as many as workgroups, however
+// many panels the matrix has.
 constexpr int64_t kOneCounterBytes = 65536;
 struct OneShape {
   int rp, n_panels, n_slices, grid;
@@ -190,9 +192,9 @@ inline bool one_shape_for(const qtea_desc& d, int batch, int max_wg, int rp, One
   if (max_wg < 1 || rp < 64 || rp % 64 != 0) return false;
   o->rp = rp;
   o->n_units = units_for(d, o->rp, &o->n_slices, &o->n_panels);
-  const int64_t per = cdiv(o->n_units, max_wg);
+  const int64_t per = cdiv(o->n_units, std::min<int64_t>(max_wg, kOneCounterBytes / 4));
   o->grid = int(cdiv(o->n_units, per));
-  o->off_part = std::max(kOneCounterBytes, align_up(4 * int64_t(o->n_panels), kAlign));
+  o->off_part = kOneCounterBytes;
   o->ws_bytes = o->off_part + 2 * int64_t(o->grid) * o->rp * batch * 4;
   return true;
 }
@@ -200,12 +202,12 @@ inline bool one_shape_for(const qtea_desc& d, int batch, int max_wg, int rp, One
 // The grouped format of one matrix at batch B: `rows` batch rows in one launch
 // (grid.y), each a batch-1 problem of its own with the runs, partial-row
 // slots and counters of `o` (those of row b behind those of row b - 1).  All
-// rows' workgroups are resident together (max_wg of them); fewer rows where
-// their counters don't fit in front of the partial rows.  ws_bytes holds for
-// every batch, so one workspace serves them all.
+// rows' workgroups are resident together (max_wg of them, one counter each).
+// ws_bytes holds for every batch, so one workspace serves them all.
 inline bool rows_shape_for(const qtea_desc& d, int batch, int max_wg, int rp, OneShape* o, int* rows) {
+  max_wg = int(std::min<int64_t>(max_wg, kOneCounterBytes / 4));
   if (!one_shape_for(d, 1, max_wg, rp, o)) return false;
-  *rows = int(std::min<int64_t>({int64_t(batch), int64_t(max_wg), o->off_part / 4 / o->n_panels}));
+  *rows = std::min(batch, max_wg);
   if (*rows > 1 && !one_shape_for(d, 1, max_wg / *rows, rp, o)) return false;
   o->ws_bytes = o->off_part + 2 * std::min<int64_t>(max_wg, o->n_units * QTEA_MAX_BATCH) * o->rp * 4;
   return true;

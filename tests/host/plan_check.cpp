@@ -444,11 +444,14 @@ void check_one(const Mat& m, int batch, int max_wg, int rp) {
   CHECK(one_first(0, U, G) == 0 && one_first(G, U, G) == U, "one: runs cover the units");
   // parts of split panels: slot 2g for the part at run g's first unit, 2g + 1
   // for a part that starts later in the run
-  std::vector<char> used(size_t(2 * G), 0);
+  // and its counter, that of its first run
+  std::vector<char> used(size_t(2 * G), 0), opened(size_t(G), 0);
   for (int64_t p = 0; p < o.n_panels; ++p) {
     const int64_t p0 = p * o.n_slices, p1 = p0 + o.n_slices;
     const int ga = one_owner(p0, U, G), gb = one_owner(p1 - 1, U, G);
     if (ga == gb) continue;
+    CHECK(!opened[size_t(ga)], "one: counter %d twice", ga);
+    opened[size_t(ga)] = 1;
     for (int g = ga; g <= gb; ++g) {
       const int64_t slot = 2 * int64_t(g) + (g == ga && p0 > one_first(g, U, G) ? 1 : 0);
       CHECK(!used[size_t(slot)], "one: slot %lld twice", (long long)slot);
@@ -456,7 +459,8 @@ void check_one(const Mat& m, int batch, int max_wg, int rp) {
       CHECK((slot + 1) * rp * batch * 4 <= o.ws_bytes - o.off_part, "one: slot past the workspace");
     }
   }
-  CHECK(o.off_part >= 4 * int64_t(o.n_panels) && o.off_part % kAlign == 0, "one: counters overlap the parts");
+  CHECK(o.off_part >= 4 * G, "one: counters overlap the parts");
+  CHECK(o.off_part == kOneCounterBytes, "one: the counters' place depends on the matrix");
 }
 
 // The grouped format's batch rows in one launch: resident together, counters
@@ -473,7 +477,8 @@ void check_rows(const Mat& m, int max_wg, int rp) {
     CHECK(rows_shape_for(d, batch, max_wg, rp, &o, &rows), "rows_shape_for");
     CHECK(rows >= 1 && rows <= batch && o.grid * rows <= max_wg, "rows: %d x %d", rows, o.grid);
     CHECK(batch > 1 || (rows == 1 && o.grid == one.grid), "rows: batch 1");
-    CHECK(4 * int64_t(rows) * o.n_panels <= o.off_part, "rows: counters overlap the parts");
+    CHECK(4 * int64_t(rows) * o.grid <= o.off_part, "rows: counters overlap the parts");
+    CHECK(o.off_part == kOneCounterBytes, "rows: the counters' place depends on the matrix");
     CHECK(8 * int64_t(o.grid) * rows * rp <= o.ws_bytes - o.off_part, "rows: slots past the workspace");
     CHECK(batch == 1 || o.ws_bytes == bytes, "rows: workspace differs by batch");
     bytes = o.ws_bytes;
@@ -624,8 +629,12 @@ int main() {
     check_one(m, 16, 256, kOneMmaRows);
     if (m.layout == kLayoutG128) check_rows(m, 512, 512);
   }
-  // 12500 panels: their counters leave room for one row per launch
+  // more panels than the counters' area has words
   check_rows(Mat{6400000, 5, 1, kLayoutG128}, 512, 512);
+  for (int wgs : {512, 7, 16384}) {
+    check_one(Mat{16416 * 512, 300, 3, kLayoutG128}, 1, wgs, 512);
+    check_rows(Mat{16416 * 512, 300, 3, kLayoutG128}, wgs, 512);
+  }
   printf("ok one-matrix runs (%d checks)\n", g_checks);
 
   check_per_device();
