@@ -42,7 +42,6 @@
 #include <vector>
 
 #include "grouped_plan.h"
-#include "per_device.h"
 
 namespace {
 
@@ -845,24 +844,12 @@ __global__ __launch_bounds__(RP / 4) void grouped_reduce_kernel(const GSplit* __
 // ---------------------------------------------------------------------------
 template <int RB, bool F8, bool G128 = false, bool ONE = false, bool ROWS = false>
 hipError_t set_lds_attr() {
-  static bool done = false;
-  if (!done) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_gemv_kernel<RB, F8, G128, ONE, ROWS>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, GLds<RB>::BYTES);
-    if (e != hipSuccess) return e;
-    done = true;
-  }
-  return hipSuccess;
+  static std::atomic<int> done[kMaxDevices];
+  return allow_lds(reinterpret_cast<const void*>(&grouped_gemv_kernel<RB, F8, G128, ONE, ROWS>), GLds<RB>::BYTES, done);
 }
 
 // A device's workgroup counts do not change: each is asked for once per device
 // (the occupancy query alone took longer than the rest of a call's host work).
-template <class Query>
-int per_current_device(std::atomic<int> (&known)[kMaxDevices], Query query) {
-  int dev = -1;
-  return hipGetDevice(&dev) == hipSuccess ? per_device(known, dev, query) : 0;
-}
-
 int cu_count() {
   static std::atomic<int> known[kMaxDevices];
   return per_current_device(known, [](int dev) {

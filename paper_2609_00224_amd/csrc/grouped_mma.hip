@@ -700,13 +700,9 @@ __global__ __launch_bounds__(RP / 4 * kRedGroups) void one_reduce_kernel(const G
 
 template <int NB, bool F8, bool ONE>
 hipError_t launch(const uint8_t* plan, int grid, float* part, const GOne& one, hipStream_t st) {
-  static bool done = false;
-  if (!done) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&grouped_mma_kernel<NB, F8, ONE>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, MLds<NB>::BYTES);
-    if (e != hipSuccess) return e;
-    done = true;
-  }
+  static std::atomic<int> done[kMaxDevices];
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(&grouped_mma_kernel<NB, F8, ONE>), MLds<NB>::BYTES, done);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((grouped_mma_kernel<NB, F8, ONE>), dim3(grid), dim3(MShape<NB, ONE>::MT), MLds<NB>::BYTES, st, plan, part,
                      one);
   return hipGetLastError();

@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include "layout.h"
+#include "per_device.h"
 #include "qtea.h"
 
 namespace qtea_detail {
@@ -63,6 +64,23 @@ __device__ __forceinline__ void store_coherent(float* p, float v) {
 }
 __device__ __forceinline__ float load_coherent(const float* p) {
   return __hip_atomic_load(const_cast<float*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// per_device of the current device.
+template <class Query>
+int per_current_device(std::atomic<int> (&known)[kMaxDevices], Query query) {
+  int dev = -1;
+  return hipGetDevice(&dev) == hipSuccess ? per_device(known, dev, query) : 0;
+}
+
+// Lets a kernel take `bytes` of dynamic LDS, once per device (`done`: one array per kernel).
+inline hipError_t allow_lds(const void* kernel, int bytes, std::atomic<int> (&done)[kMaxDevices]) {
+  hipError_t e = hipErrorInvalidDevice;
+  const int ok = per_current_device(done, [&](int) {
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    return e == hipSuccess ? 1 : 0;
+  });
+  return ok ? hipSuccess : e;
 }
 
 }  // namespace qtea_detail

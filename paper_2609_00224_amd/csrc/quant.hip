@@ -30,7 +30,6 @@
 
 #include <atomic>
 
-#include "per_device.h"
 #include "qtea_internal.h"
 #include "qtea_quant.h"
 
@@ -1079,9 +1078,7 @@ __global__ __launch_bounds__(256) void trail_gemm_kernel(double* __restrict__ Wt
 // one (256 CUs: 128; 32 CUs, which hold 64: 16).
 int block_workgroups() {
   static std::atomic<int> known[qtea_detail::kMaxDevices];
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess) return 1;
-  const int resident = qtea_detail::per_device(known, dev, [](int d) {
+  const int resident = qtea_detail::per_current_device(known, [](int d) {
     int cus = 0, per = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, d) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, reinterpret_cast<const void*>(&col_block_kernel),

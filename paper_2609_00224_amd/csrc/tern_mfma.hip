@@ -755,13 +755,9 @@ template <int NB, int WAVES, int TW, bool F8, bool ONE>
 hipError_t launch(const uint8_t* plan, int grid, float* part, const GOne& one, hipStream_t st) {
   using L = TLds<NB, WAVES, TW>;
   static_assert(L::BYTES <= 160 * 1024, "LDS of one workgroup");
-  static bool done = false;
-  if (!done) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tern_mfma_kernel<NB, WAVES, TW, F8, ONE>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, L::BYTES);
-    if (e != hipSuccess) return e;
-    done = true;
-  }
+  static std::atomic<int> done[kMaxDevices];
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(&tern_mfma_kernel<NB, WAVES, TW, F8, ONE>), L::BYTES, done);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((tern_mfma_kernel<NB, WAVES, TW, F8, ONE>), dim3(grid), dim3(WAVES * 64), L::BYTES, st, plan, part, one);
   return hipGetLastError();
 }

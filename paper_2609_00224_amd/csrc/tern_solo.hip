@@ -378,13 +378,9 @@ __global__ __launch_bounds__(kSoloWaves * 64, 4) void tern_solo_kernel(const GPr
 
 template <bool F8, int QN>
 hipError_t launch(const GProblem& pr, const SoloShape& s, int max_wg, float* part, uint32_t* counters, hipStream_t st) {
-  static bool done = false;
-  if (!done) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&tern_solo_kernel<F8, QN>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kSoloBytes);
-    if (e != hipSuccess) return e;
-    done = true;
-  }
+  static std::atomic<int> done[kMaxDevices];
+  const hipError_t e = allow_lds(reinterpret_cast<const void*>(&tern_solo_kernel<F8, QN>), kSoloBytes, done);
+  if (e != hipSuccess) return e;
   const int pieces = int(pr.n_pad >> 6) * s.split, G = std::max(1, std::min(pieces, max_wg / s.parts));
   hipLaunchKernelGGL((tern_solo_kernel<F8, QN>), dim3(uint32_t(G * s.parts)), dim3(kSoloWaves * 64), kSoloBytes, st, pr,
                      s.parts, s.chunks, part, counters);
