@@ -225,8 +225,8 @@ int qtea_gemv(const qtea_desc* desc, const void* packed, const uint16_t* x, floa
  * digits (a slice with blocks whose largest activation leaves several columns
  * below 2^-6 of it: 47 bits at batch 1, 37 at 2..8); larger matrices at 5..8 and
  * batch 9..16 on the codes in fp16 with the activations split into two fp16
- * halves; fp32 accumulation.  (The grouped format, and matrices too large for
- * the batch-1 form's workspace, run the table-lookup kernel.)
+ * halves; fp32 accumulation.  (The grouped format, and at batch 1 the sizes
+ * for which it is faster, run the table-lookup kernel.)
  * An activation that is not finite makes every output of its row NaN, as
  * 0 * inf does in the dense product.  Errors as qtea_gemv plus
  * QTEA_ERR_BATCH.

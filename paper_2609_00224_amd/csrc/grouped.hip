@@ -888,8 +888,8 @@ hipError_t launch_grouped(const uint8_t* plan, int grid, const GSplit* splits, i
   return hipGetLastError();
 }
 
-// Launch shape of one matrix on its own: batch 1 runs the task kernel (its
-// shape: solo_shape), or the table kernel (layout 4) on 512-row panels, two
+// Launch shape of one matrix on its own: batch 1 runs the task kernel or
+// the table kernel (solo_shape; layout 4: the latter) on 512-row panels, two
 // workgroups per CU at most; batch 2..16 the matrix-core kernels on 512-row
 // panels, one workgroup per CU at most.
 constexpr int kOneRB = 4;

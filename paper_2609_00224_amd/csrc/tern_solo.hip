@@ -1,6 +1,7 @@
 // One matrix times one activation row on the FP4 matrix-core path (Eq. 10 with
 // one group and zero bias, plus the Eq. 11 residual): qtea_gemv and
-// qtea_gemm_lowbatch at batch 1, layouts 2 and 3.
+// qtea_gemm_lowbatch at batch 1, layouts 2 and 3, where solo_shape takes it (the
+// table kernel is faster for few slices of many tiles and for parts of few tiles).
 //
 // What bounds it is latency: the bytes of these matrices stream in 0.5 to 4 us
 // and a launch on other units (512-row panels x 320-column slices) spent its

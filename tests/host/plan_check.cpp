@@ -28,6 +28,8 @@
 //   * one matrix on its own: the workgroup runs partition the units, none
 //     empty, one_owner inverts one_first, and the split panels' parts have
 //     distinct slots inside the workspace;
+//   * one matrix at batch 1 by tasks: every task has a wave, part sums and
+//     counters fit the workspace, and which kernel a few sizes take;
 //   * values asked for once per device: a failure is asked for again, devices
 //     do not share; and the workgroups that may wait for one another.
 #include <stdint.h>
@@ -485,6 +487,31 @@ void check_rows(const Mat& m, int max_wg, int rp) {
   }
 }
 
+// The task kernel of one matrix at batch 1, where solo_shape takes it: every task
+// has a wave, part sums and arrival counters lie in the workspace that was sized for
+// the table kernel, and the pieces of a cut tile have a workgroup each.
+// Returns whether it is taken.
+bool check_solo(const Mat& m, int max_wg) {
+  Layout L;
+  const qtea_desc d = make_desc(m, &L);
+  OneShape o;
+  CHECK(one_shape_for(d, 1, 2 * max_wg, 512, &o), "one_shape_for");
+  const SoloShape s = solo_shape(d, o, max_wg);
+  if (s.parts == 0) return false;
+  CHECK(m.layout != kLayoutG128 && s.chunks >= 1 && s.chunks <= kSoloChunks, "solo: %d chunks", s.chunks);
+  CHECK(s.split == 1 || s.split == 2 || s.split == 4, "solo: split %d", s.split);
+  const int64_t tasks = cdiv(d.n_groups, kSliceGroups) + cdiv(d.n_salient, 32 * s.chunks);
+  const int64_t pieces = d.n_pad / 64 * s.split;
+  CHECK(tasks <= int64_t(s.parts) * kSoloTasks && tasks > int64_t(s.parts - 1) * kSoloTasks, "solo: %lld tasks in %d parts",
+        (long long)tasks, s.parts);
+  CHECK(s.split == 1 || pieces * s.parts <= max_wg, "solo: %lld pieces in %d parts", (long long)pieces, s.parts);
+  if (s.parts > 1) {
+    CHECK(4 * pieces <= o.off_part, "solo: counters past their area");
+    CHECK(4 * 64 * pieces * s.parts <= o.ws_bytes - o.off_part, "solo: part sums past the workspace");
+  }
+  return true;
+}
+
 void check_per_device() {
   static std::atomic<int> known[kMaxDevices];
   int asked = 0, answer = 0;
@@ -636,6 +663,28 @@ int main() {
     check_rows(Mat{16416 * 512, 300, 3, kLayoutG128}, wgs, 512);
   }
   printf("ok one-matrix runs (%d checks)\n", g_checks);
+
+  // batch 1 by tasks: a sweep of rows and columns, none, some and all salient,
+  // around the sizes whose part sums or counters no longer fit the workspace
+  for (int64_t K : {1, 64, 320, 321, 1280, 4096, 5120, 5121, 8192, 14336, 28672})
+    for (int64_t N : {4, 60, 64, 68, 1000, 4096, 5120, 12288, 16384, 16388, 20032, 34816, 65536, 72800, 131072, 262144, 264196,
+                      1048576, 8400000})
+      for (int64_t nS : {int64_t(0), int64_t(1), K / 50, K / 20, K / 4, K})
+        if (N * K < (int64_t(1) << 31))
+          for (int layout : {kLayout, kLayoutE4M3})
+            for (int wgs : {256, 32, 7, 1}) check_solo(Mat{N, K, nS, layout}, wgs);
+  CHECK(!check_solo(Mat{4096, 4096, 82, kLayoutG128}, 256), "solo: the grouped format");
+  // either side of the line to the table kernel (measured: solo_us, table_us)
+  const Mat by_tasks[] = {{4096, 4096, 82, kLayout},    {6144, 4096, 123, kLayout}, {28672, 4096, 82, kLayout},
+                          {4096, 14336, 287, kLayout},  {8192, 8192, 410, kLayoutE4M3}, {57344, 8192, 164, kLayout},
+                          {4096, 14336, 717, kLayoutE4M3}, {64, 64, 3, kLayout},   {128256, 4096, 82, kLayout},
+                          {4096, 4096, 4096, kLayout}};
+  const Mat by_table[] = {{255016, 144, 4, kLayout},    {131072, 320, 10, kLayout}, {60744, 103, 5, kLayout},
+                          {131072, 640, 19, kLayout},   {5120, 5120, 154, kLayout}, {34816, 5120, 102, kLayoutE4M3},
+                          {100, 18763, 1876, kLayoutE4M3}, {540, 9370, 0, kLayout}, {2048, 8192, 246, kLayout}};
+  for (const Mat& m : by_tasks) CHECK(check_solo(m, 256), "%lld x %lld by tasks", (long long)m.N, (long long)m.K);
+  for (const Mat& m : by_table) CHECK(!check_solo(m, 256), "%lld x %lld by tables", (long long)m.N, (long long)m.K);
+  printf("ok batch 1 by tasks (%d checks)\n", g_checks);
 
   check_per_device();
   printf("ok values per device (%d checks)\n", g_checks);

@@ -39,5 +39,5 @@ def test_plan_records_layout_and_queue_under_sanitizers(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=env)
     assert r.returncode == 0, r.stdout + r.stderr
     for group in ("layout regions", "plan records", "planner argument checks", "chunk queue model",
-                  "one-matrix runs", "values per device"):
+                  "one-matrix runs", "batch 1 by tasks", "values per device"):
         assert f"ok {group}" in r.stdout, r.stdout
