@@ -479,6 +479,10 @@ void check_rows(const Mat& m, int max_wg, int rp) {
     CHECK(rows_shape_for(d, batch, max_wg, rp, &o, &rows), "rows_shape_for");
     CHECK(rows >= 1 && rows <= batch && o.grid * rows <= max_wg, "rows: %d x %d", rows, o.grid);
     CHECK(batch > 1 || (rows == 1 && o.grid == one.grid), "rows: batch 1");
+    // (a run's workgroups of all rows on one XCD, where their number has room)
+    CHECK(o.grid <= o.n_units && (rows == 1 || o.grid % kXcds == 0 ||
+                                  align_up(o.grid, kXcds) > std::min<int64_t>(max_wg / rows, o.n_units)),
+          "rows: %d workgroups a row", o.grid);
     CHECK(4 * int64_t(rows) * o.grid <= o.off_part, "rows: counters overlap the parts");
     CHECK(o.off_part == kOneCounterBytes, "rows: the counters' place depends on the matrix");
     CHECK(8 * int64_t(o.grid) * rows * rp <= o.ws_bytes - o.off_part, "rows: slots past the workspace");
