@@ -227,8 +227,10 @@ int qtea_gemv(const qtea_desc* desc, const void* packed, const uint16_t* x, floa
  * batch 9..16 on the codes in fp16 with the activations split into two fp16
  * halves; fp32 accumulation.  (The grouped format, and at batch 1 the sizes
  * for which it is faster, run the table-lookup kernel.)
- * An activation that is not finite makes every output of its row NaN, as
- * 0 * inf does in the dense product.  Errors as qtea_gemv plus
+ * An activation that is not finite makes every output of its batch row NaN on the
+ * matrix cores; in the table-lookup kernel it makes those outputs not finite
+ * whose code in its column is not 0 (grouped format: all of them, through the
+ * bias), and the others are NaN or keep their value.  Errors as qtea_gemv plus
  * QTEA_ERR_BATCH.
  */
 int qtea_gemm_lowbatch(const qtea_desc* desc, const void* packed, const uint16_t* X, int batch,

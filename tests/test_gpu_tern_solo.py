@@ -38,7 +38,7 @@ def test_solo_dyadic_exact(N, K, nS):
 
 @pytest.mark.parametrize("bad", [np.inf, np.nan])
 def test_activation_not_finite(bad):
-    """0 * inf is NaN: every output, as in the dense product."""
+    """Every output is NaN (the digits of its block have the NaN scale)."""
     c = dyadic_case(73, 256, 700, 1, 9)
     c["x"][0, 350] = bad
     assert np.all(np.isnan(gpu_gemm(gpu_pack(c), c["x"])))
