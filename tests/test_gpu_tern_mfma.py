@@ -43,12 +43,12 @@ def test_edges_dyadic_exact(B):
             assert np.array_equal(y.astype(np.float64), ref), ("grouped", c["N"], c["K"], B)
 
 
-@pytest.mark.parametrize("B", [3, 8])
+@pytest.mark.parametrize("B", [1, 3, 8])
 def test_wide_range_of_magnitudes(B):
-    """Activations over eight powers of ten: an a_j below its block's largest
-    by more than 2^5 keeps 2^-28 of that largest (half of it in error), so a
-    row's error is at most sum_j 2^-29 max|a| (plus 32-bit roundings of the
-    digit sums and of y, taken as 2^-22 of sum |a|)."""
+    """Activations over eight powers of ten: an a_j below 2^-6 of the largest
+    power of two of its block of 20 columns is rounded by at most 2^-28 of that
+    power, so a row's error is at most the sum of that over the row's nonzero codes
+    (plus 32-bit roundings of the digit sums and of y, 2^-22 of sum |a|)."""
     c = synth_case(71, 192, 1003, B, nS=0)
     rng = np.random.default_rng(5)
     c["x"] = (c["x"].astype(np.float64) * 10.0 ** rng.uniform(-4, 4, size=c["x"].shape)).clip(-6e4, 6e4).astype(np.float16)
@@ -56,14 +56,17 @@ def test_wide_range_of_magnitudes(B):
     y = gpu_gemm(gpu_pack(c), c["x"]).astype(np.float64)
     ref, _ = oracle_rows(c, need_wmax=False)
     a = np.abs(c["x"].astype(np.float64) * c["v"].astype(np.float64))
-    bound = c["alpha"].astype(np.float64)[None, :] * (a.shape[1] * 2.0 ** -29 * a.max(1) + 2.0 ** -22 * a.sum(1))[:, None]
+    most = np.pad(a, ((0, 0), (0, -a.shape[1] % 20))).reshape(B, -1, 20).max(2)
+    unit = np.repeat(2.0 ** np.floor(np.log2(most)), 20, axis=1)[:, : a.shape[1]]
+    nonzero = np.abs(c["trits"]).astype(np.float64)
+    bound = c["alpha"].astype(np.float64) * ((2.0 ** -28 * unit + 2.0 ** -22 * a) @ nonzero.T)
     assert np.all(np.abs(y - ref) <= bound)
 
 
 @pytest.mark.parametrize("bad", [np.inf, np.nan])
 def test_activation_not_finite(bad):
-    """0 * inf is NaN: every output of that batch row, as in the dense product;
-    the other rows keep their values."""
+    """Every output of that batch row is NaN (the digits of its block have the
+    NaN scale); the other rows keep their values."""
     c = dyadic_case(72, 256, 700, 4, 9)
     ref, _ = oracle_rows(c, need_wmax=False)
     c["x"][2, 350] = bad
