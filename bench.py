@@ -167,25 +167,30 @@ def replay_spread(g, stream, reps):
 
 
 def kernel_name(B, grouped=False, rows_per_panel=1024, e4m3=False, g128=False):
+    """The kernel of a launch as a trace names it; where the library chooses by
+    the matrix's size, every name that it may have."""
     f8 = "true" if e4m3 else "false"
+    table = f"grouped_gemv_kernel<4, {f8}, false, true, false>"
     # the grouped format runs every batch row through the batch-1 table kernel
     if grouped and g128:
-        return f"grouped_gemv_kernel<{rows_per_panel // 128}, true, true>"
+        return f"grouped_gemv_kernel<{rows_per_panel // 128}, true, true, false, false>"
     if g128:
-        return "grouped_gemv_kernel<4, true, true, true>"
+        return f"grouped_gemv_kernel<4, true, true, true, {'true' if B > 1 else 'false'}>"
     if grouped and 2 <= B <= 4:
         return f"tern_mfma_kernel<2, 8, 2, {f8}, false>"  # two result blocks of activation digits
     if grouped and B > 1:
         # hi/lo activation halves in one or two MFMAs
-        return f"grouped_mma_kernel<{1 if B <= 8 else 2}, {f8}>"
-    if grouped:
-        return f"grouped_gemv_kernel<{rows_per_panel // 128}, {f8}, false>"  # 8 waves x 16 rows per row block
+        return f"grouped_mma_kernel<{1 if B <= 8 else 2}, {f8}, false>"
+    if grouped:  # 8 waves x 16 rows per row block
+        return f"grouped_gemv_kernel<{rows_per_panel // 128}, {f8}, false, false, false>"
     # one matrix per launch (qtea_gemm_lowbatch): the same kernels in their single-problem form
-    if 2 <= B <= 8:
-        return f"tern_mfma_kernel<{2 if B <= 4 else 3}, 8, 1, {f8}, true>"
-    if B > 1:
-        return f"grouped_mma_kernel<2, {f8}, true>"
-    return f"tern_solo_kernel<{f8}>"
+    if B == 1:
+        return " / ".join([f"tern_solo_kernel<{f8}, {tiles}>" for tiles in (4, 2, 1)] + [table])
+    if B <= 4:
+        return f"tern_mfma_kernel<2, 8, 1, {f8}, true>"
+    if B <= 8:
+        return f"tern_mfma_kernel<3, 8, 1, {f8}, true> / grouped_mma_kernel<1, {f8}, true>"
+    return f"grouped_mma_kernel<2, {f8}, true>"
 
 
 def traffic_per_launch(kernel, algorithmic_bytes, workload="llama3_8b_stack batch 1"):
