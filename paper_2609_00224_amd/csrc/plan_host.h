@@ -243,11 +243,12 @@ struct SoloShape {
 // rows, 64 to 28672 columns, none to half of them salient, both formats)
 // and the layers of three decoders, weights in the cache and not, 256 CUs.
 // The chosen kernel takes 0.2 % longer than the faster one on average, over 2 %
-// longer for 1 shape in 30, 12 % at worst.  The task kernel everywhere took
-// up to 2.9 times the table kernel's time (255016 x 144, a wave or two of
-// a workgroup at work: 19.8 us against 6.9; 5120 x 5120, a second part for 5
-// more tasks: 9.6 against 8.7; 34816 x 5120: 19.2 against 17.2), the table
-// kernel everywhere up to three times the task kernel's, 30 % more on average.
+// longer for 1 shape in 35, 12 % at worst.  The task kernel everywhere took
+// up to 2.8 times the table kernel's time (255016 x 144, a wave or two of
+// a workgroup at work: 19.3 us against 6.9; 5120 x 5120, a second part for 5
+// more tasks: 9.4 against 7.5; 34816 x 5120: 18.9 against 17.3), 6 % more on
+// average, the table kernel everywhere up to three times the task kernel's, 30 %
+// more on average (28672 x 4096: 13.1 against 10.5).
 //
 // The task kernel: a start (`chunks`: the salient columns' gather), the tiles
 // walked one after another, each a barrier and the tasks' sums, and a part's
@@ -256,9 +257,9 @@ inline double solo_us(const SoloShape& s, int64_t n_tiles, int64_t tasks, int ma
   const int64_t pieces = n_tiles * s.split, here = std::min<int64_t>(tasks, kSoloTasks);
   const double walk = double(cdiv(pieces, std::max<int64_t>(1, std::min<int64_t>(pieces, max_wg / s.parts))));
   const double tile = 1.0 / s.split;  // of its 64 rows
-  return 2.51 + 0.88 * tile + 0.13 * double(here) + 0.72 * (s.chunks - 1) + (s.chunks == 3 ? 0.81 : 0.0) +
-         walk * (1.0 + 0.08 * double(here) * tile + (s.parts > 1 ? 0.2 : 0.0)) + (s.parts > 1 ? 1.48 : 0.0) +
-         0.05 * s.parts;
+  return 2.78 + 0.64 * tile + 0.17 * double(here) + 0.89 * (s.chunks - 1) + (s.chunks == 3 ? 0.39 : 0.0) +
+         walk * (0.82 + 0.08 * double(here) * tile + (s.parts > 1 ? 0.37 : 0.0)) + (s.parts > 1 ? 1.45 : 0.0) +
+         0.02 * s.parts;
 }
 // The table kernel: a start that grows with the workgroups, then units, each a
 // table, its lookups and its slice's salient columns (the first 16 or 32 of them are
@@ -268,10 +269,10 @@ inline double table_us(const qtea_desc& d, const OneShape& o, int max_wg) {
   const bool two = o.grid > max_wg;
   const bool split = o.n_slices > 1 && (o.n_units % o.grid != 0 || per % o.n_slices != 0);
   const double sal = double(d.n_salient) / o.n_slices, ahead = d.layout == kLayout ? 16.0 : 32.0;
-  return 2.33 + 5.19 * std::min(1.0, double(o.grid) / (2 * max_wg)) +
-         double(per) * (2.62 + 0.88 / 32 * std::min(sal, ahead) + (two ? 3.92 : 1.96) / 32 * std::max(0.0, sal - ahead) +
-                        (two && o.n_slices > 1 ? 0.68 : 0.0)) +
-         (split ? 1.56 + 0.02 * std::min(double(o.n_slices) / double(per), double(o.n_slices)) : 0.0);
+  return 2.58 + 0.67 * std::min(1.0, double(o.grid) / (2 * max_wg)) +
+         double(per) * ((two ? 3.58 : 2.48) + 1.28 / 32 * std::min(sal, ahead) +
+                        (two ? 5.22 : 2.61) / 32 * std::max(0.0, sal - ahead) + (two && o.n_slices > 1 ? 0.59 : 0.0)) +
+         (split ? 1.94 + 0.03 * std::min(double(o.n_slices) / double(per), double(o.n_slices)) : 0.0);
 }
 
 inline SoloShape solo_shape(const qtea_desc& d, const OneShape& o, int max_wg) {

@@ -24,14 +24,14 @@
 //
 // An activation that is not finite makes every output NaN.
 //
-// us per launch (graph of 50), the table kernel's in brackets, 3 % salient: 4096 x
-// 4096 7.1 (7.7), 6144 x 4096 7.2 (8.3), 28672 x 4096 11.0 (13.2), 4096 x 14336
-// 9.5 (12.5, four parts here), 3076 x 2999 5.9 (7.1), 512 x 700 3.7 (6.3); the 8B
-// stack's 128 products called one by one 1123 (1409) us.  Whole 64-row tiles
-// at 4096 x 4096: 7.6.  Relative L2 error against 64 bits 8e-8 to 1.1e-7 (table
+// us per launch (graph of 20), the table kernel's in brackets, 2 % salient: 4096 x
+// 4096 6.8 (7.4), 6144 x 4096 6.9 (7.3), 28672 x 4096 10.5 (13.1), 128256 x 2048
+// 17.5 (21.5), 512 x 700 3.7 (6.3); 4096 x 14336 with 5 %, four parts, 10.3 (10.5).
+// Whole 64-row tiles at 4096 x 4096: 7.6.  Relative L2 error against 64 bits 8e-8 to 1.1e-7 (table
 // sums: 1e-7 to 1.3e-7), with or without outliers of 100 to 60000 among N(0, 1)
 // activations: a slice that has some takes four more digits (tern_rest), in
-// result rows that are there anyway; looking for them costs 0.1 us.
+// result rows that are there anyway; looking for them costs 0.1 to 0.2 us, a
+// launch that finds some 0.5 to 1.
 #include <type_traits>
 
 #include "tern_common.h"

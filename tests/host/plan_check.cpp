@@ -679,13 +679,13 @@ int main() {
             for (int wgs : {256, 32, 7, 1}) check_solo(Mat{N, K, nS, layout}, wgs);
   CHECK(!check_solo(Mat{4096, 4096, 82, kLayoutG128}, 256), "solo: the grouped format");
   // either side of the line to the table kernel (measured: solo_us, table_us)
-  const Mat by_tasks[] = {{4096, 4096, 82, kLayout},    {6144, 4096, 123, kLayout}, {28672, 4096, 82, kLayout},
-                          {4096, 14336, 287, kLayout},  {8192, 8192, 410, kLayoutE4M3}, {57344, 8192, 164, kLayout},
-                          {4096, 14336, 717, kLayoutE4M3}, {64, 64, 3, kLayout},   {128256, 4096, 82, kLayout},
-                          {4096, 4096, 4096, kLayout}};
+  const Mat by_tasks[] = {{4096, 4096, 82, kLayout},    {6144, 4096, 82, kLayout}, {28672, 4096, 82, kLayout},
+                          {57344, 8192, 164, kLayout},  {4096, 14336, 717, kLayoutE4M3}, {64, 64, 3, kLayout},
+                          {128256, 4096, 82, kLayout},  {4096, 4096, 4096, kLayout}};
   const Mat by_table[] = {{255016, 144, 4, kLayout},    {131072, 320, 10, kLayout}, {60744, 103, 5, kLayout},
                           {131072, 640, 19, kLayout},   {5120, 5120, 154, kLayout}, {34816, 5120, 102, kLayoutE4M3},
-                          {100, 18763, 1876, kLayoutE4M3}, {540, 9370, 0, kLayout}, {2048, 8192, 246, kLayout}};
+                          {4096, 14336, 287, kLayout},  {8192, 8192, 410, kLayoutE4M3}, {2048, 8192, 246, kLayout},
+                          {100, 18763, 1876, kLayoutE4M3}, {540, 9370, 0, kLayout}};
   for (const Mat& m : by_tasks) CHECK(check_solo(m, 256), "%lld x %lld by tasks", (long long)m.N, (long long)m.K);
   for (const Mat& m : by_table) CHECK(!check_solo(m, 256), "%lld x %lld by tables", (long long)m.N, (long long)m.K);
   printf("ok batch 1 by tasks (%d checks)\n", g_checks);

@@ -30,12 +30,14 @@ def test_batch_5_to_8_either_side_of_two_units(N, fmt):
         _check(c, pm, B)
 
 
-# by tasks: three parts, four of half tiles, two of whole tiles, two of quarter tiles
-# with every column salient, six, as many tiles as workgroups; by tables: more
-# tiles than workgroups of one and two slices, five tasks more than one part
-# holds, a long matrix of few rows, residual tasks of 96 columns in a small one
-BATCH1 = [(4100, 14340, 287), (1028, 14336, 300), (9000, 9000, 0), (132, 1600, 1600), (4, 28672, 0), (16384, 320, 9),
-          (16388, 320, 9), (49156, 640, 19), (5124, 5120, 154), (68, 8200, 300), (260, 4096, 205)]
+# by tasks: four parts of whole tiles (in fp16), of half and of quarter ones (residual tasks
+# only in the last ones), two of whole tiles, two of quarter tiles, six, as many tiles
+# as workgroups; by tables: three parts, more tiles than workgroups of one and two
+# slices, five tasks more than one part holds, a long matrix of few rows, residual
+# tasks of 96 columns in a small one
+BATCH1 = [(4100, 14340, 1500), (2048, 4096, 4096), (1024, 4096, 4096), (9000, 9000, 0), (132, 1600, 1600), (4, 28672, 0),
+          (16384, 320, 9), (4100, 14340, 287), (16388, 320, 9), (49156, 640, 19), (5124, 5120, 154), (68, 8200, 300),
+          (260, 4096, 205)]
 
 
 @pytest.mark.parametrize("fmt", ["fp16", "e4m3"])
