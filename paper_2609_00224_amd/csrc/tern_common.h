@@ -129,7 +129,7 @@ __device__ __forceinline__ void tern_fixed(const float (&a)[5], float (&f)[5], u
 // activations pass the line in one of 500 slices.
 template <int ND>
 __device__ __forceinline__ bool tern_rest(const float (&a)[5], float (&f)[5], uint32_t ex, uint32_t top) {
-  if (__ballot(top == 0u) == 0) return false;
+  if (__builtin_expect(__ballot(top == 0u) == 0, 1)) return false;
   uint32_t low = 0;
   bool left = false;
   float r[5];
@@ -140,7 +140,7 @@ __device__ __forceinline__ bool tern_rest(const float (&a)[5], float (&f)[5], ui
     low += __builtin_fabsf(f[i]) < 0x1p21f ? 1u : 0u;
   }
   low = quad_sum(low);
-  if (__ballot(left && low >= 5u) == 0) return false;  // (zeros are small and leave nothing)
+  if (__builtin_expect(__ballot(left && low >= 5u) == 0, 1)) return false;  // (zeros are small and leave nothing)
 #pragma unroll
   for (int i = 0; i < 5; ++i) f[i] = __builtin_rintf(r[i] * float(1 << (5 * ND - 1)));
   return true;

@@ -30,8 +30,9 @@
 // Whole 64-row tiles at 4096 x 4096: 7.6.  Relative L2 error against 64 bits 8e-8 to 1.1e-7 (table
 // sums: 1e-7 to 1.3e-7), with or without outliers of 100 to 60000 among N(0, 1)
 // activations: a slice that has some takes four more digits (tern_rest), in
-// result rows that are there anyway; looking for them costs 0.1 to 0.2 us, a
-// launch that finds some 0.5 to 1.
+// result rows that are there anyway.  Looking for them costs 0.1 us (0.2 with their
+// code in line with the rest, where every launch fetched it), a launch that
+// finds some 0.5 to 1.
 #include <type_traits>
 
 #include "tern_common.h"
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(kSoloWaves * 64, 4) void tern_solo_kernel(const GPr
     tern_fixed(a, f, ex, mx);
     operands(std::integral_constant<int, kDigits>{}, true, [&](int l) { return tern_scale(ex, mx, l); });  // result rows 8..15 repeat 0..7 ...
     const bool rest = tern_rest<kSoloRest>(a, f, ex, top);
-    if (rest)
+    if (__builtin_expect(rest, 0))
       operands(std::integral_constant<int, kSoloRest>{}, n16 >= 8, [&](int l) { return tern_rest_scale<kSoloRest>(ex, mx, l); });  // ... or are the second set's
     __syncthreads();  // the decode table is complete
     walk([&](int t, int tn, uint32_t out) {
@@ -247,7 +248,7 @@ __global__ __launch_bounds__(kSoloWaves * 64, 4) void tern_solo_kernel(const GPr
         const float s6 = (s4 + C[q][2]) + C[q][3];
         const float mine = (kg & 1) ? s4 : s6;
         float s = mine + __shfl_xor(mine, 16);
-        if (rest) s += __shfl(s6, lane | 32);  // (uniform; lane group 0's is stored)
+        if (__builtin_expect(rest, 0)) s += __shfl(s6, lane | 32);  // (uniform; lane group 0's is stored)
 #ifdef QTEA_DEBUG
         if ((bad >> q) & 1u) s = __builtin_nanf("");
 #endif
