@@ -14,9 +14,12 @@ pytestmark = pytest.mark.gpu
 # (N, K, salient): 16 slices and none, one column more (two parts), 13 slices
 # with 3, 4 and 9 tasks of 32 salient columns (96 a task keeps one part), all
 # columns salient, rows around a tile and its pieces, 64 / 65 / 128 / 129 / 257 tiles
+# (four of them are the table kernel's by now: 5121 and 14336 columns, 288 and 289
+# salient columns of 4096); several parts with tasks of 32, 64 and 96 salient
+# columns and one part with 96, which are the task kernel's
 SHAPES = [(64, 5120, 0), (68, 5121, 0), (132, 4096, 96), (60, 4096, 97), (256, 4096, 288), (4, 4096, 289), (8, 1, 1),
           (192, 700, 700), (4096, 1601, 33), (4100, 4800, 31), (8192, 640, 5), (8196, 640, 64), (16388, 321, 20),
-          (320, 14336, 700)]
+          (320, 14336, 700), (4096, 2999, 600), (516, 1603, 1603), (68, 3200, 3200), (1028, 6000, 2500), (28672, 4096, 205)]
 
 
 @pytest.mark.parametrize("N,K,nS", SHAPES)
